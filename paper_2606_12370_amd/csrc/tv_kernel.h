@@ -84,6 +84,36 @@ __device__ inline double chain_factors(const double* al, int K, int mode, double
   return 1.0 - sum / K;
 }
 
+// The same for one step k, the overlaps read through al(i) (the products and
+// sums in chain_factors' order): g = dL/dalpha_k and the position loss L.
+template <class Alpha>
+__device__ __forceinline__ void chain_factor_of(int K, int mode, int k, Alpha al, double* g, double* L) {
+  double pre = 1.0, pre_k = 1.0, sum = 0.0, lin = 0.0;
+  for (int i = 0; i < K; ++i) {
+    if (i == k) pre_k = pre;
+    const double ai = al(i);
+    pre *= ai;
+    sum += pre;
+    lin += 1.0 - ai;
+  }
+  double suf = 1.0, tail = 1.0;  // prod over i > k; 1 + alpha_{i} tail, from the last step down to k + 1
+  for (int i = K - 1; i > k; --i) {
+    const double ai = al(i);
+    suf *= ai;
+    tail = 1.0 + ai * tail;
+  }
+  if (mode == kModePerStep) {
+    *g = -1.0 / K;
+    *L = lin / K;
+  } else if (mode == kModeProd) {
+    *g = -(pre_k * suf);
+    *L = -pre;
+  } else {
+    *g = -(pre_k * tail) / K;
+    *L = 1.0 - sum / K;
+  }
+}
+
 template <class E>
 __device__ __forceinline__ void tv_rows(const TvArgs& a, int n, int k, int* rt_i, int* rd_i) {
   *rt_i = n * a.K + k;

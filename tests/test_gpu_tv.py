@@ -143,3 +143,49 @@ def test_target_masked_tokens(mode, dtype):
     loss, ov, grad, ref = run_case(d, mode, 0.9, scale=0.5)
     assert np.all(np.isfinite(ref["grad"]))
     print(mode, dtype, compare_tv(loss, ov, grad, ref, dtype))
+
+
+@pytest.mark.parametrize("mode", ["e2e", "prod", "per_step"])
+@pytest.mark.parametrize("N,K,V,dtype", [
+    (3, 2, 4, W.BF16),            # one vector per row
+    (5, 3, 2048, W.BF16),         # one whole tile of a slice
+    (5, 3, 2052, W.BF16),         # a second tile of one vector
+    (2, 8, 38 * 2048, W.BF16),    # the most tiles one slice holds
+    (2, 8, 38 * 2048 + 4, W.BF16),
+    (300, 1, 16 * 2048 - 8, W.BF16),   # more positions than groups: several per group, the last round partial
+    (70, 4, 80 * 1024 + 12, W.BF16),   # the same with slices exchanging records
+    (2, 3, 19 * 2048 + 4, W.F32),
+    (2, 8, 262144, W.F32),        # more slices than a position may take: the two-read passes
+])
+def test_single_read_edges(N, K, V, dtype, mode):
+    """The gradient call over aligned rows at the edges of its tiles, slices
+    and position groups, against the oracle (a few positions of the long
+    calls), and twice the same bits."""
+    g = np.random.default_rng(V + K)
+    d = W.tv_inputs_numpy(N, K, V, dtype, 900 + K, noise=g.uniform(0.05, 2.0, N))
+    tgt, drf = device_inputs(d)
+    a = binding.tv_loss_fwd_bwd(tgt, drf, 0.8, mode, 0.5)
+    b = binding.tv_loss_fwd_bwd(tgt, drf, 0.8, mode, 0.5)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    pos = np.unique(np.linspace(0, N - 1, min(N, 6)).astype(int))
+    ref = oracle.tv_ref(W.to_float64(d["target"][pos], dtype), W.to_float64(d["draft"][pos], dtype),
+                        float(np.float32(0.8)), MODES[mode], 0.5, want_grad=True)
+    ref["scale"] = 0.5
+    compare_tv(a[0], a[1], a[2], ref, dtype, positions=pos, loss_exact=len(pos) == N)
+    # the total loss from the call's own overlaps
+    al = a[1].cpu().numpy().astype(np.float64)
+    total = 0.5 * chain_factors(al, MODES[mode])[1].sum()
+    assert abs(float(a[0]) - total) <= 1e-5 * abs(total) + 1e-6 * N * K
+
+
+def test_single_read_data_errors():
+    """NaN or infinite logits make that position's loss and gradient NaN."""
+    for bad in (np.nan, np.inf):
+        d = W.tv_inputs_numpy(3, 2, 4096, W.F32, 8)
+        d["target"][1, 0, 77] = bad
+        tgt, drf = device_inputs(d)
+        loss, ov, grad = binding.tv_loss_fwd_bwd(tgt, drf, 1.0, "e2e", 1.0)
+        torch.cuda.synchronize()
+        assert torch.isnan(loss).all() and torch.isnan(ov[1, 0]) and torch.isnan(grad[1]).all()
+        assert torch.isfinite(grad[0]).all() and torch.isfinite(grad[2]).all() and torch.isfinite(ov[0]).all()
