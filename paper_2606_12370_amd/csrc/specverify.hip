@@ -20,6 +20,7 @@
 #include "variants_kernel.h"
 #include "verify_kernel.h"
 #include "fused_kernel.h"
+#include "resident_kernel.h"
 
 namespace {
 
@@ -420,8 +421,107 @@ spec_status launch_sample_gumbel(const sv::GumbelSampleArgs& a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
+// ---- single-read TV loss: launch facts per device ---------------------------
+struct ResFacts {
+  std::atomic<int> ready{0};
+  int slots[2] = {0, 0};  // workgroups of each instantiation the device holds at once
+};
+ResFacts g_res_facts[kMaxDevices];
+std::mutex g_res_mu;
+
+const ResFacts* res_facts() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+  ResFacts& f = g_res_facts[dev];
+  if (f.ready.load(std::memory_order_acquire)) return &f;
+  std::lock_guard<std::mutex> lk(g_res_mu);
+  if (!f.ready.load(std::memory_order_relaxed)) {
+    int cus = 0, nb = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+    const void* kern[2];
+    kern[SPEC_BF16] = reinterpret_cast<const void*>(&sv::tv_resident_kernel<sv::BF16H, sv::ResCap<sv::BF16H>::NV>);
+    kern[SPEC_F32] = reinterpret_cast<const void*>(&sv::tv_resident_kernel<F32, sv::ResCap<F32>::NV>);
+    for (int i = 0; i < 2; ++i) {
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern[i], sv::kResThreads, 0) != hipSuccess) nb = 0;
+      f.slots[i] = nb * cus;
+    }
+    (void)hipGetLastError();
+    f.ready.store(1, std::memory_order_release);
+  }
+  return &f;
+}
+
+struct ResPlan {
+  int G = 0, groups = 0, tiles = 0;
+};
+
+// Slices per row and position groups for a call of N positions, or G = 0
+// where the pair does not fit the registers of the workgroups one position
+// may take.  A group's time per position is about its tiles per slice (0.7
+// us each) plus eleven tiles' time for the exchanges; the slices are chosen
+// for the shortest run of ceil(N / groups) positions.
+ResPlan res_plan(int N, int K, int V, int nv, int epv, int slots) {
+  ResPlan p;
+  const int tile = sv::kResThreads * epv;
+  const int tiles = static_cast<int>((static_cast<int64_t>(V) + tile - 1) / tile);
+  int64_t best = 0;
+  for (int G = (tiles + nv - 1) / nv; G <= sv::kResMaxSlices && G <= tiles && K * G <= sv::kResMaxGroup; ++G) {
+    const int groups = std::min(N, slots / (K * G));
+    if (groups < 1) break;
+    const int64_t cost = static_cast<int64_t>((N + groups - 1) / groups) * ((tiles + G - 1) / G + 11);
+    if (p.G == 0 || cost < best) {
+      best = cost;
+      p.G = G;
+      p.groups = groups;
+      p.tiles = tiles;
+    }
+  }
+  return p;
+}
+
+// The single-read pass for calls with a gradient over aligned rows of whole
+// vectors.  Without a gradient its exchanges are not hidden behind any
+// writes: N = 4096, K = 3, V = 151936 bfloat16 2.52 ms against 2.43 for the
+// passes that read twice.
+template <class E>
+bool launch_tv_resident(const sv::TvArgs& a, void* ws, hipStream_t s, spec_status* st) {
+  const spec_dtype dt = std::is_same<E, BF16>::value ? SPEC_BF16 : SPEC_F32;
+  using G = typename GradElem<E>::type;
+  constexpr int NV = sv::ResCap<G>::NV;
+  const size_t es = esize_of(dt), align = es * G::EPV;
+  const sv::RowsDesc& d = a.rows;
+  auto fits = [&](const void* p, int64_t s0, int64_t s1) {
+    return reinterpret_cast<uintptr_t>(p) % align == 0 && static_cast<uint64_t>(s0) * es % align == 0 &&
+           static_cast<uint64_t>(s1) * es % align == 0;
+  };
+  if (d.V % G::EPV != 0 || !fits(d.tgt, d.tsb, d.tsk) || !fits(d.drf, d.dsb, d.dsk)) return false;
+  if (!a.grad || !a.vec_g) return false;
+  const ResFacts* f = res_facts();
+  if (!f || f->slots[dt] <= 0) return false;
+  const ResPlan p = res_plan(a.N, a.K, d.V, NV, G::EPV, f->slots[dt]);
+  if (p.G == 0) return false;
+  sv::ResArgs r;
+  r.G = p.G;
+  r.tiles = p.tiles;
+  r.groups = p.groups;
+  r.head = static_cast<uint32_t*>(ws);
+  r.rec = static_cast<uint64_t*>(ws) + sv::kResHeadWords;
+  r.spin_limit = 1u << 20;  // about a second of polling, never reached (see the kernel)
+  const int64_t words = sv::kResHeadWords + int64_t{a.N} * a.K * p.G * sv::kResWords;
+  hipLaunchKernelGGL(sv::fill_ones_kernel, dim3(static_cast<unsigned>(std::min<int64_t>((words + 255) / 256, 1024))),
+                     dim3(sv::kThreads), 0, s, static_cast<uint64_t*>(ws), words);
+  void (*k)(sv::TvArgs, sv::ResArgs) = sv::tv_resident_kernel<G, NV>;
+  hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(p.groups * a.K * p.G)), dim3(sv::kResThreads), 0, s, a, r);
+  hipLaunchKernelGGL(sv::tv_resident_loss_kernel, dim3(1), dim3(sv::kThreads), 0, s, a,
+                     static_cast<const uint32_t*>(r.head));
+  *st = hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
+  return true;
+}
+
 template <class E, int NT>
-spec_status launch_tv(const sv::TvArgs& a, hipStream_t s) {
+spec_status launch_tv(const sv::TvArgs& a, void* res_ws, hipStream_t s) {
+  spec_status st;
+  if (launch_tv_resident<E>(a, res_ws, s, &st)) return st;
   const int64_t units = int64_t{a.N} * a.K;
   const int C = a.rows.C;
   // the statistics per sub-chunk of kStep tiles with the wave-shaped pass,
@@ -832,7 +932,8 @@ spec_status spec_tv_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, 
   a.bits = grad_draft ? reinterpret_cast<uint8_t*>(ws + L.bits) : nullptr;
   a.bits_stride = static_cast<int64_t>(L.bits_stride);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return dtype == SPEC_BF16 ? launch_tv<BF16, kNtBf16>(a, s) : launch_tv<F32, kNtF32>(a, s);
+  void* res_ws = ws + L.bits;  // the exchange records of the single-read pass, in the indicator words' place
+  return dtype == SPEC_BF16 ? launch_tv<BF16, kNtBf16>(a, res_ws, s) : launch_tv<F32, kNtF32>(a, res_ws, s);
 }
 
 size_t spec_verify_target_only_workspace_size(int B, int K, int V, spec_dtype dtype) {
