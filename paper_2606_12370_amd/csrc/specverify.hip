@@ -384,6 +384,17 @@ spec_status launch_verify(const sv::VerifyArgs& a, int64_t rows, hipStream_t s, 
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
+// Parts per row of the Gumbel scans, one workgroup each: about `wgs`
+// workgroups in all, at most one part per chunk (the workspace holds one
+// record per chunk).  A workgroup that scans more of its row knows a better
+// key sooner, more of them balance rows of different cost.  Measured without
+// overlaps at B = 256, K = 3, V = 151936: 512 / 768 / 1024 / 1280 / 1600 /
+// 2560 workgroups 158 / 150 / 146 / 147 / 150 / 154 us; the sampler with 768
+// rows: 2560 / 5120 / 7680 workgroups 111 / 106 / 108 us.
+constexpr int kScanWgsVerify = 1024;
+constexpr int kScanWgsSample = 5120;
+int scan_parts(int rows, int C, int wgs) { return std::max(1, std::min(C, (wgs + rows - 1) / rows)); }
+
 template <class E, int NT>
 spec_status launch_verify_gumbel(const sv::VerifyArgs& a, sv::GumbelBest* gbest, int64_t rows, hipStream_t s) {
   const int C = a.rows.C;
@@ -400,22 +411,26 @@ spec_status launch_verify_gumbel(const sv::VerifyArgs& a, sv::GumbelBest* gbest,
     hipLaunchKernelGGL(pp, dim3(static_cast<unsigned>(pairs)), dim3(sv::kThreads), 0, s, a,
                        pairs);
   }
-  void (*gp)(sv::VerifyArgs, sv::GumbelBest*, int64_t) = sv::gumbel_pass_kernel<E, NT, kStep>;
-  const int64_t tasks = int64_t{a.B} * C;
-  hipLaunchKernelGGL(gp, dim3(static_cast<unsigned>(tasks)), dim3(sv::kThreads), 0, s, a,
-                     gbest, tasks);
+  const int P = scan_parts(a.B, C, kScanWgsVerify);
+  hipLaunchKernelGGL((sv::gumbel_pass_kernel<E>), dim3(static_cast<unsigned>(int64_t{a.B} * P)), dim3(sv::kThreads), 0,
+                     s, a, gbest, P);
   hipLaunchKernelGGL(sv::gumbel_finish_kernel, dim3(static_cast<unsigned>((a.B + sv::kWaves - 1) / sv::kWaves)),
-                     dim3(sv::kThreads), 0, s, a, static_cast<const sv::GumbelBest*>(gbest));
+                     dim3(sv::kThreads), 0, s, a, static_cast<const sv::GumbelBest*>(gbest), P);
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
-template <class E, int NT>
-spec_status launch_sample_gumbel(const sv::GumbelSampleArgs& a, hipStream_t s) {
-  const int64_t tasks = int64_t{a.R} * a.rows.C;
-  // two tiles per load step (153.5-153.9 against 160.9-161.3 us per call for
-  // 768 rows of V=151936 bf16)
-  void (*gp)(sv::GumbelSampleArgs, int64_t) = sv::gumbel_sample_pass_kernel<E, NT, 2>;
-  hipLaunchKernelGGL(gp, dim3(static_cast<unsigned>(tasks)), dim3(sv::kThreads), 0, s, a, tasks);
+template <class E>
+spec_status launch_sample_gumbel(sv::GumbelSampleArgs a, hipStream_t s) {
+  a.P = scan_parts(a.R, a.rows.C, kScanWgsSample);
+  // parts beyond the first round of what the device holds start with the best
+  // key of the earlier ones (rows with one dominant token 127 -> 87 us; one
+  // more small launch)
+  a.share = a.P > 1 && int64_t{a.R} * a.P > 1280 ? 1 : 0;
+  if (a.share)
+    hipLaunchKernelGGL(sv::gumbel_sample_init_kernel, dim3(static_cast<unsigned>((a.R + sv::kThreads - 1) / sv::kThreads)),
+                       dim3(sv::kThreads), 0, s, a);
+  hipLaunchKernelGGL((sv::gumbel_sample_pass_kernel<E>), dim3(static_cast<unsigned>(int64_t{a.R} * a.P)),
+                     dim3(sv::kThreads), 0, s, a);
   hipLaunchKernelGGL(sv::gumbel_sample_finish_kernel, dim3(static_cast<unsigned>((a.R + sv::kWaves - 1) / sv::kWaves)),
                      dim3(sv::kThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
@@ -883,7 +898,7 @@ spec_status spec_sample_gumbel(const void* logits, int64_t stride_r, spec_dtype 
   a.token = tokens;
   a.best = reinterpret_cast<sv::GumbelBest*>(workspace);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return dtype == SPEC_BF16 ? launch_sample_gumbel<BF16, kNtBf16>(a, s) : launch_sample_gumbel<F32, kNtF32>(a, s);
+  return dtype == SPEC_BF16 ? launch_sample_gumbel<BF16>(a, s) : launch_sample_gumbel<F32>(a, s);
 }
 
 spec_status spec_tv_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, int64_t t_stride_k,

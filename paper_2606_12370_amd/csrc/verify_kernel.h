@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void pair_pass_kernel(VerifyArgs a, int64
     const int u = static_cast<int>(t / C), c = static_cast<int>(t - static_cast<int64_t>(t / C) * C);
     const int b = u / a.K, i = u % a.K;
     const int n = a.decision[b];
-    if (n < 0) continue;  // data error: the finish ignores this row's partials
+    if (n < 0 || i == n) continue;  // data error, or the step whose overlap the Gumbel pass sums
     const int rt_i = target_row(a, b, i), rd_i = draft_row(a, b, i);
     int bb;
     bool al_t, al_d;

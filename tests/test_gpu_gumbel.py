@@ -182,3 +182,66 @@ def test_sample_gumbel_benchmark_draft_rows():
     ri = torch.as_tensor(rows, device="cuda")
     ref = sample_gumbel_ref(host_logits(flat[ri], W.BF16), T[ri].cpu().numpy().astype(np.float64), 9, 4, rows=rows)
     print(compare_sample_gumbel(out["tokens"], ref, rows=rows))
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("V", [5, 8, 2047, 2048, 2056, 16384 + 8, 50001])
+def test_sampler_scan_bounds(V, dtype):
+    """Rows whose elements mostly need no variate (one or a few logits far
+    above the rest, at either end of the row), rows where every element does,
+    masked rows, equal logits and large scales, at the edges of the scan's
+    blocks and parts: the tokens of the oracle, which draws every variate."""
+    R = 24
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((R, V)).astype(np.float32)
+    z[0:4] *= 8.0
+    z[4, V - 1] = 30.0
+    z[5, 0] = 30.0
+    z[6, V // 2] = 18.0
+    z[7, :] = 1.5                                  # all equal
+    z[8, : V // 2] = -np.inf                       # masked halves
+    z[9, V // 2:] = -np.inf
+    z[10, 1:] = -np.inf                            # one token left
+    z[11] *= 1000.0
+    z[12] = z[12] * 0.01 + 300.0
+    z[13] = z[13] * 0.01 - 300.0
+    z[14, V - 1] = np.nan
+    z[15, V // 3] = np.inf
+    z[16, :] = -np.inf
+    T = np.ones(R, np.float32)
+    T[17] = 0.05
+    T[18] = 20.0
+    T[19] = 0.0
+    d = W.f32_to_bf16_bits(z) if dtype == W.BF16 else z
+    lg = torch.from_numpy(d.view(np.int16)).cuda().view(torch.bfloat16) if dtype == W.BF16 else torch.from_numpy(d).cuda()
+    pad = torch.zeros((R, V + 9), dtype=lg.dtype, device="cuda")
+    pad[:, 1:V + 1] = lg
+    out = binding.sample_gumbel(lg, torch.from_numpy(T).cuda(), seed=11, offset=3)["tokens"]
+    odd = binding.sample_gumbel(pad[:, 1:V + 1], torch.from_numpy(T).cuda(), seed=11, offset=3)["tokens"]
+    torch.cuda.synchronize()
+    ref = sample_gumbel_ref(W.to_float64(d, dtype), T.astype(np.float64), 11, 3)
+    compare_sample_gumbel(out, ref)
+    assert torch.equal(out, odd)
+
+
+@pytest.mark.parametrize("V", [9, 2 * 2048, 2 * 2048 + 3, 40000])
+def test_verify_scan_parts_without_residual_mass(V):
+    """Rejected steps whose residual has mass in one half of the row only (the
+    draft holds nearly all of its mass in the other), so that the parts of
+    the other half fall back to p_n and must not win."""
+    B, K = 32, 2
+    rng = np.random.default_rng(V + 1)
+    tgt = rng.standard_normal((B, K + 1, V)).astype(np.float32) * 3
+    drf = tgt[:, :K].copy()
+    half = V // 2
+    drf[: B // 2, :, half:] += 20.0
+    drf[B // 2:, :, :half] += 20.0
+    ids = rng.integers(0, half, (B, K)).astype(np.int32)
+    ids[: B // 2] += V - half
+    T = np.ones(B, np.float32)
+    out = binding.verify(torch.from_numpy(tgt).cuda(), torch.from_numpy(drf).cuda(), torch.from_numpy(ids).cuda(),
+                         torch.from_numpy(T).cuda(), seed=4, offset=1, gumbel=True)
+    torch.cuda.synchronize()
+    ref = verify_gumbel_ref(tgt.astype(np.float64), drf.astype(np.float64), ids, T.astype(np.float64), 4, 1)
+    assert (ref["accept_len"] < K).sum() >= B // 4  # rejections to look at
+    print(compare_verify_gumbel(out, ref, W.F32))
