@@ -25,8 +25,8 @@
  *  - Work is only enqueued on `stream` (a hipStream_t passed as void*, NULL =
  *    the null stream); no call synchronises with the host.
  *  - Host-checkable argument errors are returned synchronously before any
- *    work is enqueued.  Misaligned pointers or strides are not an error:
- *    they select element-wise loads instead of 16-byte vector loads.
+ *    work is enqueued.  Pointers and strides need only
+ *    element alignment: the kernels' vector loads and stores take any.
  *  - The workspace is scratch memory: it needs no initialisation, each call
  *    overwrites what it reads, and no state is carried from one call to the
  *    next.  Calls that share a workspace must not run concurrently (enqueue

@@ -145,7 +145,7 @@ struct Block8 {
     const int off = v0 + 8 <= V ? v0 : 0;
 #pragma unroll
     for (int h = 0; h < NV; ++h)
-      w[h] = __builtin_nontemporal_load(reinterpret_cast<const typename E::vec*>(row + off) + h);
+      w[h] = load_vec<E>(row + off + h * E::EPV);
   }
   __device__ __forceinline__ void widen(float (&x)[8]) const {
 #pragma unroll
@@ -172,8 +172,8 @@ __device__ __forceinline__ void block_elements(const typename E::raw* row, int v
 // Every thread receives the results: Key::kNone and kNoIndex where no element
 // counts.  *bad (sampler): whether a weight is NaN or +inf.
 template <class E, class Key, bool BOTH, class Weight>
-__device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, bool al_x, const typename E::raw* ry, bool al_y,
-                                            int e0, int e1, int V, uint64_t c0, uint64_t c2, uint64_t tag,
+__device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typename E::raw* ry, int e0,
+                                            int e1, int V, uint64_t c0, uint64_t c2, uint64_t tag,
                                             uint64_t seed, Weight weight, int* row_best, ScanShared& sh,
                                             RedLds<4>& red, RedLds<1>& red1, float* best, int* index, bool* bad) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -182,7 +182,7 @@ __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, bool al_x
   int bi = kNoIndex;
   bool isbad = false;
   int qn = 0;  // entries of this wave's queue
-  const bool vec = al_x && (!BOTH || al_y) && V >= 8;
+  const bool vec = V >= 8;
   constexpr int STEP = kScanTile * kScanBlocks;
   Block8<E> nx[kScanBlocks], ny[kScanBlocks];
   auto load = [&](int es) {
@@ -304,9 +304,9 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   if (n < 0) return;  // data error: decide has written the row
   const bool residual = n < K;
   int bb, e0, e1;
-  bool al_t, al_d, bad;
-  const typename E::raw* rt = row_of<E>(d, target_row(a, b, n), &bb, &al_t);
-  const typename E::raw* rd = row_of<E>(d, draft_row(a, b, residual ? n : 0), &bb, &al_d);
+  bool bad;
+  const typename E::raw* rt = row_of<E>(d, target_row(a, b, n), &bb);
+  const typename E::raw* rd = row_of<E>(d, draft_row(a, b, residual ? n : 0), &bb);
   const float s = scale_of(temperature_of(d, b));
   const RowNorm nt = a.norms[target_row(a, b, n)];
   const RowNorm nd = a.norms[draft_row(a, b, residual ? n : 0)];
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   if (residual) {
     float al = 0.f;
     gumbel_scan<E, KeyRatio, true>(
-        rt, al_t, rd, al_d, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
+        rt, rd, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
         [&](const float (&x)[8], const float (&y)[8], float (&r)[8]) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   // mass, of which every part is without
   if (!(o.kr > 0.f)) {
     gumbel_scan<E, KeyRatio, false>(
-        rt, al_t, rt, al_t, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
+        rt, rt, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
         [&](const float (&x)[8], const float (&)[8], float (&r)[8]) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) r[k] = prob(x[k], s, nt.M, nt.invD);
@@ -423,8 +423,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_sample_pass_kernel(GumbelSamp
   // with the best key of the parts before it
   const int part = static_cast<int>(blockIdx.x) / a.R, r = static_cast<int>(blockIdx.x) - part * a.R;
   int bb, e0, e1;
-  bool al;
-  const typename E::raw* row = row_of<E>(d, r, &bb, &al);
+  const typename E::raw* row = row_of<E>(d, r, &bb);
   const float T = temperature_of(d, r);
   const float s = temperature_ok(T) ? scale_of(T) : 1.0f;
   scan_part(V, P, part, &e0, &e1);
@@ -435,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_sample_pass_kernel(GumbelSamp
     for (int es = e0; es < e1; es += kScanTile) {
       const int v0 = es + static_cast<int>(threadIdx.x) * 8;
       float x[8];
-      if (al && v0 + 8 <= V) {
+      if (v0 + 8 <= V) {
         Block8<E> w;
         w.load(row, v0, V);
         w.widen(x);
@@ -455,7 +454,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_sample_pass_kernel(GumbelSamp
     bad = m[1] > 0.f;
   } else {
     gumbel_scan<E, KeyScore, false>(
-        row, al, row, al, e0, e1, V, static_cast<uint64_t>(r), a.offset, kTagGumbelSample, a.seed,
+        row, row, e0, e1, V, static_cast<uint64_t>(r), a.offset, kTagGumbelSample, a.seed,
         [&](const float (&x)[8], const float (&)[8], float (&w)[8]) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) w[k] = x[k] * s;

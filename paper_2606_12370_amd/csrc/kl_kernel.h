@@ -107,7 +107,6 @@ struct KlArgs {
   float4* coef;          // [N K]: reverse KL the gradient factor and mu - c; forward KL, CE lam_t - lam_d as hi + lo
   double pair_limit;     // forward KL, CE: |lam_t - lam_d| up to which x is summed pairwise
   double* loss_pos;      // [N]
-  int vec_g;
 };
 
 // 2^(z s - r).  With CORR the exponent is carried beyond float32: z s = h + l
@@ -144,8 +143,7 @@ __global__ __launch_bounds__(kThreads) void kl_stats_wave_kernel(RowsDesc d, int
   if (g >= nsub) return;
   const int r = static_cast<int>(g / SC), j = static_cast<int>(g - static_cast<int64_t>(g / SC) * SC);
   int b;
-  bool aligned;
-  const typename E::raw* row = row_of<E>(d, r, &b, &aligned);
+  const typename E::raw* row = row_of<E>(d, r, &b);
   const float s = scale_of(d.temp_scalar);
   const int e0 = j * WV * 64 * EPV;
   float zm = -INFINITY, rf = 0.f;
@@ -156,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void kl_stats_wave_kernel(RowsDesc d, int
     const int es = e0 + st * S * 64 * EPV;
     if (es >= d.V) break;
     float x[S][EPV];
-    load_span<E, S, 64>(row, es, lane, d.V, aligned, x);
+    load_span<E, S, 64>(row, es, lane, d.V, x);
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < S; ++i)
@@ -278,12 +276,11 @@ __global__ __launch_bounds__(kThreads) void kl_top_kernel(RowsDesc d, const KlSt
   int idx = d.V;
   if (c0 < SC) {
     int b;
-    bool al;
-    const typename E::raw* rd = row_of<E>(d, NK + u, &b, &al);
+    const typename E::raw* rd = row_of<E>(d, NK + u, &b);
     const int e0 = c0 * SUB, e1 = min(d.V, e0 + SUB);
     for (int es = e0; es < e1; es += S * 64 * EPV) {
       float x[S][EPV];
-      load_span<E, S, 64>(rd, es, lane, d.V, al, x);
+      load_span<E, S, 64>(rd, es, lane, d.V, x);
 #pragma unroll
       for (int j = 0; j < S; ++j)
 #pragma unroll
@@ -298,8 +295,7 @@ __global__ __launch_bounds__(kThreads) void kl_top_kernel(RowsDesc d, const KlSt
     float zo = norms[u].zmax;
     if (idx < d.V) {
       int b;
-      bool al;
-      zo = E::one(row_of<E>(d, u, &b, &al) + idx);
+      zo = E::one(row_of<E>(d, u, &b) + idx);
     }
     norms[NK + u].zo = zo;
   }
@@ -401,14 +397,14 @@ __device__ __forceinline__ float kl_fwd_grad(float e, float f, float dl, const K
   return mx > 0.f ? gcoef * copysignf(g, dl) : (mx == 0.f ? 0.f : mx);
 }
 
-// Write EPV gradient values of one vector (float4 stores when aligned).
+// Write EPV gradient values of one vector (16-byte stores at any alignment).
 template <int EPV>
-__device__ __forceinline__ void store_grad(float* gr, int v0, int V, bool vec, const float (&gv)[EPV]) {
-  if (vec && v0 + EPV <= V) {
+__device__ __forceinline__ void store_grad(float* gr, int v0, int V, const float (&gv)[EPV]) {
+  if (v0 + EPV <= V) {
 #pragma unroll
     for (int h = 0; h < EPV; h += 4) {
       f32x4 w4 = {gv[h], gv[h + 1], gv[h + 2], gv[h + 3]};
-      __builtin_nontemporal_store(w4, reinterpret_cast<f32x4*>(gr + v0 + h));
+      __builtin_nontemporal_store(w4, reinterpret_cast<f32x4_any*>(gr + v0 + h));
     }
   } else {
 #pragma unroll
@@ -433,10 +429,10 @@ __device__ __forceinline__ bool kl_needs_pairwise(const KlNorm& t, const KlNorm&
 // pairwise x.  With GW (forward KL / CE beyond the pair limit, dr carrying
 // lam_t - lam_d of the two normalisers) the task also writes its gradient.
 template <class E, int NT, int S, int KIND, bool X, bool GW>
-__device__ __forceinline__ void kl_pass_sums(const typename E::raw* rt, bool al_t, const typename E::raw* rd,
-                                             bool al_d, int tile0, int nt_tiles, int V, float s, const KlNorm& nt,
+__device__ __forceinline__ void kl_pass_sums(const typename E::raw* rt, const typename E::raw* rd, int tile0,
+                                             int nt_tiles, int V, float s, const KlNorm& nt,
                                              const KlNorm& nd, const KlDelta& dr, double (&v)[4], float* gr,
-                                             float gcoef, bool vec_g) {
+                                             float gcoef) {
   constexpr int EPV = E::EPV;
   constexpr int TILE = kThreads * EPV;
   double se = 0.0, sf = 0.0, w = 0.0, xs = 0.0;
@@ -450,8 +446,8 @@ __device__ __forceinline__ void kl_pass_sums(const typename E::raw* rt, bool al_
   for (int j0 = 0; j0 < NT; j0 += S) {
     if (j0 >= nt_tiles) break;
     float xt[S][EPV], xd[S][EPV];
-    load_tiles<E, S>(rt, tile0 + j0, V, al_t, xt);
-    load_tiles<E, S>(rd, tile0 + j0, V, al_d, xd);
+    load_tiles<E, S>(rt, tile0 + j0, V, xt);
+    load_tiles<E, S>(rd, tile0 + j0, V, xd);
 #pragma unroll
     for (int j = 0; j < S; ++j) {
       // the EPV elements of one vector are summed in float32, vectors in float64
@@ -491,7 +487,7 @@ __device__ __forceinline__ void kl_pass_sums(const typename E::raw* rt, bool al_
       sf += static_cast<double>(vf);
       w += static_cast<double>(vw);
       if (KIND == kKlReverse || X) xs += static_cast<double>(vx);
-      if (GW) store_grad<EPV>(gr, (tile0 + j0 + j) * TILE + static_cast<int>(threadIdx.x) * EPV, V, vec_g, gv);
+      if (GW) store_grad<EPV>(gr, (tile0 + j0 + j) * TILE + static_cast<int>(threadIdx.x) * EPV, V, gv);
     }
   }
   v[0] = se; v[1] = sf; v[2] = w; v[3] = xs;
@@ -508,9 +504,8 @@ __global__ __launch_bounds__(kThreads) void kl_pass_kernel(KlArgs a, int64_t nta
   for (int64_t t = blockIdx.x; t < ntasks; t += gridDim.x) {
     const int u = static_cast<int>(t / C), c = static_cast<int>(t - static_cast<int64_t>(t / C) * C);
     int bb;
-    bool al_t, al_d;
-    const typename E::raw* rt = row_of<E>(d, u, &bb, &al_t);
-    const typename E::raw* rd = row_of<E>(d, NK + u, &bb, &al_d);
+    const typename E::raw* rt = row_of<E>(d, u, &bb);
+    const typename E::raw* rd = row_of<E>(d, NK + u, &bb);
     const float s = scale_of(d.temp_scalar);
     const KlNorm nt = a.norms[u], nd = a.norms[NK + u];
     const KlDelta dr = KIND == kKlReverse ? kl_delta_top(nd, s) : kl_delta_ref(nt, nd, s);
@@ -524,14 +519,12 @@ __global__ __launch_bounds__(kThreads) void kl_pass_kernel(KlArgs a, int64_t nta
     // beyond it the gradient needs nothing but the two normalisers and is
     // written here, so kl_grad skips the pair.
     if (KIND != kKlReverse && kl_needs_pairwise(nt, nd, a.pair_limit))
-      kl_pass_sums<E, NT, S, KIND, true, false>(rt, al_t, rd, al_d, tile0, nt_tiles, V, s, nt, nd, dr, v, gr, gcoef,
-                                                a.vec_g != 0);
+      kl_pass_sums<E, NT, S, KIND, true, false>(rt, rd, tile0, nt_tiles, V, s, nt, nd, dr, v, gr, gcoef);
     else if (KIND != kKlReverse && gr)
-      kl_pass_sums<E, NT, SN, KIND, false, true>(rt, al_t, rd, al_d, tile0, nt_tiles, V, s, nt, nd, dr, v, gr, gcoef,
-                                                 a.vec_g != 0);
+      kl_pass_sums<E, NT, SN, KIND, false, true>(rt, rd, tile0, nt_tiles, V, s, nt, nd, dr, v, gr, gcoef);
     else
-      kl_pass_sums<E, NT, SN, KIND, false, false>(rt, al_t, rd, al_d, tile0, nt_tiles, V, s, nt, nd, dr, v, gr,
-                                                  gcoef, a.vec_g != 0);
+      kl_pass_sums<E, NT, SN, KIND, false, false>(rt, rd, tile0, nt_tiles, V, s, nt, nd, dr, v, gr,
+                                                  gcoef);
     wg_sum<4>(v, red);
     if (threadIdx.x == 0) {
       KlPart o;
@@ -630,9 +623,8 @@ __global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t nta
     const int c0 = kPerPair ? 0 : static_cast<int>(it - static_cast<int64_t>(u) * C);
     const int c1 = kPerPair ? C : c0 + 1;
     int bb;
-    bool al_t, al_d;
-    const typename E::raw* rt = row_of<E>(d, u, &bb, &al_t);
-    const typename E::raw* rd = row_of<E>(d, NK + u, &bb, &al_d);
+    const typename E::raw* rt = row_of<E>(d, u, &bb);
+    const typename E::raw* rd = row_of<E>(d, NK + u, &bb);
     const float s = scale_of(d.temp_scalar);
     const KlNorm nt = a.norms[u], nd = a.norms[NK + u];
     if (KIND != kKlReverse && !kl_needs_pairwise(nt, nd, a.pair_limit)) continue;  // written by kl_pass
@@ -647,8 +639,8 @@ __global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t nta
       for (int j0 = 0; j0 < NT; j0 += S) {
         if (j0 >= nt_tiles) break;
         float xt[S][EPV], xd[S][EPV];
-        load_tiles<E, S>(rt, tile0 + j0, V, al_t, xt);
-        load_tiles<E, S>(rd, tile0 + j0, V, al_d, xd);
+        load_tiles<E, S>(rt, tile0 + j0, V, xt);
+        load_tiles<E, S>(rd, tile0 + j0, V, xd);
 #pragma unroll
         for (int j = 0; j < S; ++j) {
           float gv[EPV];
@@ -664,7 +656,7 @@ __global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t nta
               gv[k] = kl_fwd_grad<E>(e, f, rk.dl, nt, nd, gcoef);
             }
           }
-          store_grad<EPV>(gr, (tile0 + j0 + j) * TILE + static_cast<int>(threadIdx.x) * EPV, V, a.vec_g != 0, gv);
+          store_grad<EPV>(gr, (tile0 + j0 + j) * TILE + static_cast<int>(threadIdx.x) * EPV, V, gv);
         }
       }
     }

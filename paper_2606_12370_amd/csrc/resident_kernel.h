@@ -74,6 +74,23 @@ __device__ __forceinline__ u32x4 res_neg_inf(const F32*) {
   return u32x4{0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u};
 }
 
+// The vector's elements moved down by n (0 to 4), -inf from the top.
+__device__ __forceinline__ void res_shift(u32x2& w, int n) {
+  const uint64_t ninf = 0xFF80FF80FF80FF80ull;
+  uint64_t v = (static_cast<uint64_t>(w.y) << 32) | w.x;
+  v = n == 0 ? v : (n >= 4 ? ninf : (v >> (16 * n)) | (ninf << (64 - 16 * n)));
+  w.x = static_cast<uint32_t>(v);
+  w.y = static_cast<uint32_t>(v >> 32);
+}
+__device__ __forceinline__ void res_shift(u32x4& w, int n) {
+  const uint32_t ninf = 0xFF800000u;
+  const uint32_t a = w.x, b = w.y, c = w.z, d = w.w;
+  w.x = n == 0 ? a : (n == 1 ? b : (n == 2 ? c : (n == 3 ? d : ninf)));
+  w.y = n == 0 ? b : (n == 1 ? c : (n == 2 ? d : ninf));
+  w.z = n == 0 ? c : (n == 1 ? d : ninf);
+  w.w = n == 0 ? d : ninf;
+}
+
 // Opaque to the compiler: values derived from a held register (widened
 // logits, tile conditions) are formed again after this point instead of being
 // kept in registers of their own.
@@ -221,13 +238,16 @@ __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, R
 #pragma unroll
   for (int j = 0; j < NV; ++j) xt[j] = xd[j] = res_neg_inf(static_cast<const E*>(nullptr));
 
-  // byte offset of this thread's vector inside a tile; in the last slot a
-  // vector past the row is read from the tile's start and masked
+  // byte offset of this thread's vector inside a tile; in the last slot the
+  // last `over` elements of a vector lie past the row: the row's last whole
+  // vector is read in its place, shifted down and filled with -inf
   const uint32_t voff = static_cast<uint32_t>(tid) * sizeof(vec);
-  const bool past = (tb + NV - 1) * TILE + tid * EPV >= V;
+  const int vlast = (tb + NV - 1) * TILE + tid * EPV;
+  const int over = min(max(vlast + EPV - V, 0), EPV);
   auto tile_load = [&](const typename E::raw* row, int j) -> vec {
+    if (j == NV - 1) return load_vec<E>(row + (over > 0 ? V - EPV : vlast));
     const char* base = reinterpret_cast<const char*>(row + static_cast<int64_t>(tb + j) * TILE);
-    return __builtin_nontemporal_load(reinterpret_cast<const vec*>(base + (j == NV - 1 && past ? 0u : voff)));
+    return load_any(reinterpret_cast<const typename E::any*>(base + voff));
   };
   auto row_t = [&](int n) {
     return static_cast<const typename E::raw*>(d.tgt) + static_cast<int64_t>(n) * d.tsb + static_cast<int64_t>(k) * d.tsk;
@@ -245,8 +265,8 @@ __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, R
       }
   }
   for (int n = grp; n < a.N; n += r.groups) {
-    // vectors past the row (the row's last tile only) hold -inf
-    if (past) xt[NV - 1] = xd[NV - 1] = res_neg_inf(static_cast<const E*>(nullptr));
+    res_shift(xt[NV - 1], over);
+    res_shift(xd[NV - 1], over);
     float mt, md;
     double Dt, Dd;
     res_stats<E, NV>(xt, s, &mt, &Dt);
@@ -398,8 +418,13 @@ __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, R
         g.z = o[2] * (o[2] < 0.f ? nA0 : A1);
         g.w = o[3] * (o[3] < 0.f ? nA0 : A1);
         char* base = reinterpret_cast<char*>(gr + static_cast<int64_t>(tb + j) * TILE);
-        if (j < NV - 1 || !past)
-          __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(base + static_cast<uint32_t>(tid) * 16u));
+        if (j < NV - 1 || over == 0) {
+          __builtin_nontemporal_store(g, reinterpret_cast<f32x4_any*>(base + static_cast<uint32_t>(tid) * 16u));
+        } else {
+          if (over < 4) gr[vlast] = g.x;
+          if (over < 3) gr[vlast + 1] = g.y;
+          if (over < 2) gr[vlast + 2] = g.z;
+        }
         if (more) {
           xt[j] = tile_load(rt, j);
           xd[j] = tile_load(rd, j);

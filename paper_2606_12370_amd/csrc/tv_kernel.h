@@ -49,7 +49,6 @@ struct TvArgs {
   double* loss_pos;      // [N]
   uint8_t* bits;         // [N K][bits_stride]: 1[q <= p] per element, one 64-bit word per (chunk, tv_pair thread); NULL without gradient
   int64_t bits_stride;   // bytes per (position, step)
-  int vec_g;
 };
 
 constexpr int kModeE2E = 0;
@@ -150,10 +149,9 @@ __global__ __launch_bounds__(kThreads) void tv_pair_kernel(TvArgs a, int64_t nta
     const int u = static_cast<int>(t / C), c = static_cast<int>(t - static_cast<int64_t>(t / C) * C);
     const int n = u / a.K, k = u % a.K;
     int rt_i, rd_i, bb;
-    bool al_t, al_d;
     tv_rows<E>(a, n, k, &rt_i, &rd_i);
-    const typename E::raw* rt = row_of<E>(d, rt_i, &bb, &al_t);
-    const typename E::raw* rd = row_of<E>(d, rd_i, &bb, &al_d);
+    const typename E::raw* rt = row_of<E>(d, rt_i, &bb);
+    const typename E::raw* rd = row_of<E>(d, rd_i, &bb);
     const float s = scale_of(d.temp_scalar);
     const RowNorm nt = a.norms[rt_i], nd = a.norms[rd_i];
     const int tile0 = c * NT;
@@ -165,8 +163,8 @@ __global__ __launch_bounds__(kThreads) void tv_pair_kernel(TvArgs a, int64_t nta
     for (int j0 = 0; j0 < NT; j0 += S) {
       if (j0 >= nt_tiles) break;
       float xt[S][EPV], xd[S][EPV];
-      load_tiles<E, S>(rt, tile0 + j0, d.V, al_t, xt);
-      load_tiles<E, S>(rd, tile0 + j0, d.V, al_d, xd);
+      load_tiles<E, S>(rt, tile0 + j0, d.V, xt);
+      load_tiles<E, S>(rd, tile0 + j0, d.V, xd);
 #pragma unroll
       for (int j = 0; j < S; ++j) {
         uint32_t m = 0;
@@ -248,9 +246,8 @@ __global__ __launch_bounds__(kThreads) void tv_grad_kernel(TvArgs a, int64_t nta
     const int u = static_cast<int>(t / C), c = static_cast<int>(t - static_cast<int64_t>(t / C) * C);
     const int n = u / K, k = u % K;
     int rt_i, rd_i, bb;
-    bool al_d;
     tv_rows<E>(a, n, k, &rt_i, &rd_i);
-    const typename E::raw* rd = row_of<E>(d, rd_i, &bb, &al_d);
+    const typename E::raw* rd = row_of<E>(d, rd_i, &bb);
     const float s = scale_of(d.temp_scalar);
     const RowNorm nd = a.norms[rd_i];
     const float2 A = a.coef[u];
@@ -270,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void tv_grad_kernel(TvArgs a, int64_t nta
         const int v0 = (tile0 + j0 + j) * TILE + static_cast<int>(threadIdx.x) * EPV;
         le[j] = v0 < V ? load_bits4<EPVW>(rb, c, v0 - c * NT * TILE) : 0u;
       }
-      load_tiles<E, S>(rd, tile0 + j0, V, al_d, xd);
+      load_tiles<E, S>(rd, tile0 + j0, V, xd);
 #pragma unroll
       for (int j = 0; j < S; ++j) {
         const int v0 = (tile0 + j0 + j) * TILE + threadIdx.x * EPV;
@@ -280,11 +277,11 @@ __global__ __launch_bounds__(kThreads) void tv_grad_kernel(TvArgs a, int64_t nta
           const float q = prob(xd[j][kk], s, nd.M, nd.invD);
           gv[kk] = q * (((le[j] >> kk) & 1u) ? A.x : A.y);
         }
-        if (a.vec_g && v0 + EPV <= V) {
+        if (v0 + EPV <= V) {
 #pragma unroll
           for (int h = 0; h < EPV; h += 4) {
             f32x4 w4 = {gv[h], gv[h + 1], gv[h + 2], gv[h + 3]};
-            __builtin_nontemporal_store(w4, reinterpret_cast<f32x4*>(gr + v0 + h));
+            __builtin_nontemporal_store(w4, reinterpret_cast<f32x4_any*>(gr + v0 + h));
           }
         } else {
 #pragma unroll

@@ -75,8 +75,7 @@ __global__ __launch_bounds__(kThreads) void to_verify_kernel(ToArgs a) {
       x = a.ids[static_cast<int64_t>(b) * K + tid];
       if (x >= 0 && x < V) {
         int bb;
-        bool al;
-        zx = E::one(row_of<E>(d, row0 + tid, &bb, &al) + x);
+        zx = E::one(row_of<E>(d, row0 + tid, &bb) + x);
       }
     }
     const Philox4x64 g = philox4x64_10(static_cast<uint64_t>(b), static_cast<uint64_t>(tid), a.offset, 0ull,
@@ -133,8 +132,7 @@ __global__ __launch_bounds__(kThreads) void to_verify_kernel(ToArgs a) {
   const int excl = sh.excl;
   const RowNorm nn = sh.nrm[n];
   int bb;
-  bool al;
-  const raw* rt = row_of<E>(d, row0 + n, &bb, &al);
+  const raw* rt = row_of<E>(d, row0 + n, &bb);
   const RowStat* st = a.stats + static_cast<int64_t>(row0 + n) * C;
   // wave 0, lane cc < 64: the mass of sub-chunk cc from its statistics,
   // requested before the chunk holding x_n is read
@@ -148,7 +146,7 @@ __global__ __launch_bounds__(kThreads) void to_verify_kernel(ToArgs a) {
   double xm = 0.0;
   if (cx >= 0) {
     float tsum[NT];
-    const int ntl = tile_masses<E, NT, S>(rt, al, rt, al, false, excl, cx, V, d.ntiles, s, nn, nn, kNoResidual, tsum);
+    const int ntl = tile_masses<E, NT, S>(rt, rt, false, excl, cx, V, d.ntiles, s, nn, nn, kNoResidual, tsum);
     double W[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) W[j] = (j < ntl) ? static_cast<double>(tsum[j]) : 0.0;
@@ -178,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void to_verify_kernel(ToArgs a) {
   __syncthreads();
   int token = -1;
   if (sh.cstar >= 0)
-    token = sample_in_chunk<E, NT, S>(rt, al, rt, al, false, sh.excl_on ? excl : -1, sh.cstar, sh.tin, V, d.ntiles,
+    token = sample_in_chunk<E, NT, S>(rt, rt, false, sh.excl_on ? excl : -1, sh.cstar, sh.tin, V, d.ntiles,
                                       s, nn, nn, kNoResidual, redv, red1, sh.smp);
   if (tid == 0) a.emitted[static_cast<int64_t>(b) * (K + 1) + n] = token;
 }
@@ -203,7 +201,7 @@ struct SampleKShared {
 
 // First index of the value M inside chunk c (whole workgroup; INT_MAX if absent).
 template <class E, int NT, int S>
-__device__ __forceinline__ int first_index_of(const typename E::raw* row, bool aligned, int c, float M, int V,
+__device__ __forceinline__ int first_index_of(const typename E::raw* row, int c, float M, int V,
                                               int ntiles, RedLds<1>& red1) {
   constexpr int EPV = E::EPV;
   constexpr int TILE = kThreads * EPV;
@@ -214,7 +212,7 @@ __device__ __forceinline__ int first_index_of(const typename E::raw* row, bool a
   for (int j0 = 0; j0 < NT; j0 += S) {
     if (j0 >= nt_tiles) break;
     float x[S][EPV];
-    load_tiles<E, S>(row, tile0 + j0, V, aligned, x);
+    load_tiles<E, S>(row, tile0 + j0, V, x);
 #pragma unroll
     for (int j = 0; j < S; ++j)
 #pragma unroll
@@ -266,15 +264,14 @@ __global__ __launch_bounds__(kThreads) void sample_kernel(SampleArgs a) {
   }
   __syncthreads();
   int bb;
-  bool al;
-  const raw* row = row_of<E>(d, r, &bb, &al);
+  const raw* row = row_of<E>(d, r, &bb);
   int token = -1;
   if (sh.ok && sh.cstar >= 0) {
     if (greedy) {
-      const int v = first_index_of<E, NT, S>(row, al, sh.cstar, sh.nrm.M, V, d.ntiles, red1);
+      const int v = first_index_of<E, NT, S>(row, sh.cstar, sh.nrm.M, V, d.ntiles, red1);
       token = v == 0x7fffffff ? -1 : v;
     } else {
-      token = sample_in_chunk<E, NT, S>(row, al, row, al, false, -1, sh.cstar, sh.tin, V, d.ntiles, s, sh.nrm,
+      token = sample_in_chunk<E, NT, S>(row, row, false, -1, sh.cstar, sh.tin, V, d.ntiles, s, sh.nrm,
                                         sh.nrm, kNoResidual, redv, red1, sh.smp);
     }
   }
@@ -349,8 +346,7 @@ __global__ __launch_bounds__(kThreads) void diag_stats_wave_kernel(RowsDesc d, D
   const int C = d.C;
   const int r = static_cast<int>(g / C), j = static_cast<int>(g - static_cast<int64_t>(g / C) * C);
   int b;
-  bool aligned;
-  const typename E::raw* row = row_of<E>(d, r, &b, &aligned);
+  const typename E::raw* row = row_of<E>(d, r, &b);
   const float T = temperature_of(d, b);
   const float s = temperature_ok(T) ? scale_of(T) : 1.0f;
   const int e0 = j * WV * 64 * EPV;
@@ -361,7 +357,7 @@ __global__ __launch_bounds__(kThreads) void diag_stats_wave_kernel(RowsDesc d, D
     const int es = e0 + st * S * 64 * EPV;
     if (es >= d.V) break;  // wave-uniform: the row's last sub-chunk may be short
     float x[S][EPV];
-    load_span<E, S, 64>(row, es, lane, d.V, aligned, x);
+    load_span<E, S, 64>(row, es, lane, d.V, x);
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < S; ++i)
@@ -414,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void diag_stats_wave_kernel(RowsDesc d, D
       if (st == zstep) {
         const int es = e0 + st * S * 64 * EPV;
         float x[S][EPV];
-        load_span<E, S, 64>(row, es, lane, d.V, aligned, x);
+        load_span<E, S, 64>(row, es, lane, d.V, x);
 #pragma unroll
         for (int i = S - 1; i >= 0; --i)
 #pragma unroll
@@ -448,9 +444,8 @@ __global__ __launch_bounds__(kThreads) void diag_pair_wave_kernel(DiagArgs a, in
   if (g >= nitems) return;  // the whole wave leaves: nothing below synchronises the workgroup
   const int u = static_cast<int>(g / C), j = static_cast<int>(g - static_cast<int64_t>(g / C) * C);
   int b;
-  bool al_t, al_d;
-  const typename E::raw* rt = row_of<E>(d, u, &b, &al_t);
-  const typename E::raw* rd = row_of<E>(d, BK + u, &b, &al_d);
+  const typename E::raw* rt = row_of<E>(d, u, &b);
+  const typename E::raw* rd = row_of<E>(d, BK + u, &b);
   const float T = temperature_of(d, b);
   const float s = temperature_ok(T) ? scale_of(T) : 1.0f;
   const RowNorm nt = a.norms[u], nd = a.norms[BK + u];
@@ -461,8 +456,8 @@ __global__ __launch_bounds__(kThreads) void diag_pair_wave_kernel(DiagArgs a, in
     const int es = e0 + st * S * 64 * EPV;
     if (es >= d.V) break;  // wave-uniform: the row's last sub-chunk may be short
     float xt[S][EPV], xd[S][EPV];
-    load_span<E, S, 64>(rt, es, lane, d.V, al_t, xt);
-    load_span<E, S, 64>(rd, es, lane, d.V, al_d, xd);
+    load_span<E, S, 64>(rt, es, lane, d.V, xt);
+    load_span<E, S, 64>(rd, es, lane, d.V, xd);
 #pragma unroll
     for (int i = 0; i < S; ++i)
 #pragma unroll
@@ -542,8 +537,7 @@ __global__ __launch_bounds__(kThreads) void diag_finish_kernel(DiagArgs a) {
   ge = wave_sum(ge);
   if (lane != 0) return;
   int b;
-  bool al;
-  const raw* rt = row_of<E>(d, u, &b, &al);
+  const raw* rt = row_of<E>(d, u, &b);
   const float T = temperature_of(d, b);
   const RowNorm nt = a.norms[u], nd = a.norms[BK + u];
   const DiagRow it = a.info[u], id = a.info[BK + u];

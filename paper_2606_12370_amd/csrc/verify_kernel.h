@@ -157,9 +157,8 @@ __device__ __forceinline__ DraftGather gather_draft(const VerifyArgs& a, int b, 
   g.u = u24(ph.w[0]);
   if (g.x >= 0 && g.x < d.V) {
     int bb;
-    bool al;
-    g.zt = E::one(row_of<E>(d, target_row(a, b, i), &bb, &al) + g.x);
-    g.zd = E::one(row_of<E>(d, draft_row(a, b, i), &bb, &al) + g.x);
+    g.zt = E::one(row_of<E>(d, target_row(a, b, i), &bb) + g.x);
+    g.zd = E::one(row_of<E>(d, draft_row(a, b, i), &bb) + g.x);
   }
   return g;
 }
@@ -274,9 +273,8 @@ __global__ __launch_bounds__(kThreads) void pair_pass_kernel(VerifyArgs a, int64
     if (n < 0 || i == n) continue;  // data error, or the step whose overlap the Gumbel pass sums
     const int rt_i = target_row(a, b, i), rd_i = draft_row(a, b, i);
     int bb;
-    bool al_t, al_d;
-    const typename E::raw* rt = row_of<E>(d, rt_i, &bb, &al_t);
-    const typename E::raw* rd = row_of<E>(d, rd_i, &bb, &al_d);
+    const typename E::raw* rt = row_of<E>(d, rt_i, &bb);
+    const typename E::raw* rd = row_of<E>(d, rd_i, &bb);
     const float s = scale_of(temperature_of(d, b));
     const RowNorm nt = a.norms[rt_i], nd = a.norms[rd_i];
     const int tile0 = c * NT;
@@ -286,8 +284,8 @@ __global__ __launch_bounds__(kThreads) void pair_pass_kernel(VerifyArgs a, int64
     for (int j0 = 0; j0 < NT; j0 += S) {
       if (j0 >= nt_tiles) break;
       float xt[S][EPV], xd[S][EPV];
-      load_tiles<E, S>(rt, tile0 + j0, d.V, al_t, xt);
-      load_tiles<E, S>(rd, tile0 + j0, d.V, al_d, xd);
+      load_tiles<E, S>(rt, tile0 + j0, d.V, xt);
+      load_tiles<E, S>(rd, tile0 + j0, d.V, xd);
 #pragma unroll
       for (int j = 0; j < S; ++j)
 #pragma unroll
@@ -311,15 +309,15 @@ struct StepSums {
 };
 
 template <class E, int S>
-__device__ __forceinline__ StepSums pair_step_sums(const typename E::raw* rt, const typename E::raw* rd, bool al_t,
-                                                   bool al_d, int es, int lane, int V, float s, const RowNorm& nt,
+__device__ __forceinline__ StepSums pair_step_sums(const typename E::raw* rt, const typename E::raw* rd, int es,
+                                                   int lane, int V, float s, const RowNorm& nt,
                                                    const RowNorm& nd, bool need_z, const ResidualRef& rr, float rft,
                                                    float rfd) {
   constexpr int EPV = E::EPV;
   StepSums o = {{0.f, 0.f, 0.f, 0.f}};
   float xt[S][EPV], xd[S][EPV];
-  load_span<E, S, 64>(rt, es, lane, V, al_t, xt);
-  load_span<E, S, 64>(rd, es, lane, V, al_d, xd);
+  load_span<E, S, 64>(rt, es, lane, V, xt);
+  load_span<E, S, 64>(rd, es, lane, V, xd);
   if (need_z) {
 #pragma unroll
     for (int q = 0; q < S; ++q)
@@ -436,9 +434,8 @@ __device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, i
   if (!need_z && a.overlap == nullptr) return;  // no overlap requested: only the residual step is read again
   const int rt_i = target_row(a, b, i), rd_i = draft_row(a, b, i);
   int bb;
-  bool al_t, al_d;
-  const typename E::raw* rt = row_of<E>(d, rt_i, &bb, &al_t);
-  const typename E::raw* rd = row_of<E>(d, rd_i, &bb, &al_d);
+  const typename E::raw* rt = row_of<E>(d, rt_i, &bb);
+  const typename E::raw* rd = row_of<E>(d, rd_i, &bb);
   const float s = scale_of(temperature_of(d, b));
   const RowNorm nt = a.norms[rt_i], nd = a.norms[rd_i];
   const ResidualRef rr = need_z ? residual_ref(nt, nd, 0.0) : kNoResidual;
@@ -452,7 +449,7 @@ __device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, i
     for (int st = wave * NW; st < (wave + 1) * NW; ++st) {
       const int es = e0 + st * S * 64 * EPV;
       StepSums ps = {{0.f, 0.f, 0.f, 0.f}};
-      if (es < d.V) ps = pair_step_sums<E, S>(rt, rd, al_t, al_d, es, lane, d.V, s, nt, nd, need_z, rr, rft, rfd);
+      if (es < d.V) ps = pair_step_sums<E, S>(rt, rd, es, lane, d.V, s, nt, nd, need_z, rr, rft, rfd);
 #pragma unroll
       for (int q = 0; q < 4; ++q) part[st][q][lane] = ps.v[q];
     }
@@ -470,7 +467,7 @@ __device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, i
     for (int st = 0; st < NS; ++st) {
       const int es = e0 + st * S * 64 * EPV;
       if (es >= d.V) break;  // wave-uniform: the row's last sub-chunk may be short
-      const StepSums ps = pair_step_sums<E, S>(rt, rd, al_t, al_d, es, lane, d.V, s, nt, nd, true, rr, rft, rfd);
+      const StepSums ps = pair_step_sums<E, S>(rt, rd, es, lane, d.V, s, nt, nd, true, rr, rft, rfd);
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[q] += static_cast<double>(ps.v[q]);
     }
@@ -479,7 +476,7 @@ __device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, i
     for (int st = 0; st < NS; ++st) {
       const int es = e0 + st * S * 64 * EPV;
       if (es >= d.V) break;  // wave-uniform: the row's last sub-chunk may be short
-      const StepSums ps = pair_step_sums<E, S>(rt, rd, al_t, al_d, es, lane, d.V, s, nt, nd, false, rr, rft, rfd);
+      const StepSums ps = pair_step_sums<E, S>(rt, rd, es, lane, d.V, s, nt, nd, false, rr, rft, rfd);
       acc[0] += static_cast<double>(ps.v[0]);
     }
   }
@@ -554,8 +551,8 @@ struct SampleShared {
 // (`residual`, residual_mass), else p; element `excl` (-1: none) has mass 0.
 // Returns the number of tiles in the chunk.
 template <class E, int NT, int S>
-__device__ __forceinline__ int tile_masses(const typename E::raw* rt, bool al_t, const typename E::raw* rd,
-                                           bool al_d, bool residual, int excl, int c, int V, int ntiles, float s,
+__device__ __forceinline__ int tile_masses(const typename E::raw* rt, const typename E::raw* rd, bool residual,
+                                           int excl, int c, int V, int ntiles, float s,
                                            const RowNorm& nt, const RowNorm& nd, const ResidualRef& rr,
                                            float (&tsum)[NT], float (*keep)[S][E::EPV] = nullptr) {
   constexpr int EPV = E::EPV;
@@ -572,8 +569,8 @@ __device__ __forceinline__ int tile_masses(const typename E::raw* rt, bool al_t,
   for (int j0 = 0; j0 < NT; j0 += S) {
     if (j0 >= nt_tiles) break;
     float xt[S][EPV], xd[S][EPV];
-    load_tiles<E, S>(rt, tile0 + j0, V, al_t, xt);
-    if (residual) load_tiles<E, S>(rd, tile0 + j0, V, al_d, xd);
+    load_tiles<E, S>(rt, tile0 + j0, V, xt);
+    if (residual) load_tiles<E, S>(rd, tile0 + j0, V, xd);
 #pragma unroll
     for (int j = 0; j < S; ++j)
 #pragma unroll
@@ -592,8 +589,8 @@ __device__ __forceinline__ int tile_masses(const typename E::raw* rt, bool al_t,
 // masses of that tile, then an element scan in the winning thread.  Every
 // thread returns the token (-1 if the chunk has no mass).
 template <class E, int NT, int S>
-__device__ int sample_in_chunk(const typename E::raw* rt, bool al_t, const typename E::raw* rd, bool al_d,
-                               bool residual, int excl, int cstar, double tin, int V, int ntiles, float s,
+__device__ int sample_in_chunk(const typename E::raw* rt, const typename E::raw* rd, bool residual,
+                               int excl, int cstar, double tin, int V, int ntiles, float s,
                                const RowNorm& nt, const RowNorm& nd, const ResidualRef& rr, RedLds<NT>& redv,
                                RedLds<1>& red1, SampleShared& sh) {
   constexpr int EPV = E::EPV;
@@ -603,7 +600,7 @@ __device__ int sample_in_chunk(const typename E::raw* rt, bool al_t, const typen
   float tsum[NT];
   // a chunk of one load step keeps its element masses for the final scan
   float keep[S][EPV];
-  const int nt_tiles = tile_masses<E, NT, S>(rt, al_t, rd, al_d, residual, excl, cstar, V, ntiles, s, nt, nd, rr,
+  const int nt_tiles = tile_masses<E, NT, S>(rt, rd, residual, excl, cstar, V, ntiles, s, nt, nd, rr,
                                              tsum, NT == S ? &keep : nullptr);
   double W[NT];
 #pragma unroll
@@ -823,13 +820,12 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(VerifyArgs a) {
   int token = -1;
   if (sh.cstar >= 0) {
     int bb;
-    bool al_t, al_d;
-    const raw* rt = row_of<E>(d, target_row(a, b, n), &bb, &al_t);
-    const raw* rd = row_of<E>(d, draft_row(a, b, n < K ? n : 0), &bb, &al_d);
+    const raw* rt = row_of<E>(d, target_row(a, b, n), &bb);
+    const raw* rd = row_of<E>(d, draft_row(a, b, n < K ? n : 0), &bb);
     const RowNorm nt = sh.nrm[n];
     const RowNorm nd = sh.nrm[K + 1 + (n < K ? n : 0)];
     const ResidualRef rr = residual_ref(nt, nd, sh.w);
-    token = sample_in_chunk<E, NT, S>(rt, al_t, rd, al_d, sh.residual != 0, -1, sh.cstar, sh.tin, V, d.ntiles, s, nt,
+    token = sample_in_chunk<E, NT, S>(rt, rd, sh.residual != 0, -1, sh.cstar, sh.tin, V, d.ntiles, s, nt,
                                       nd, rr, redv, red1, sh.smp);
   }
 

@@ -155,6 +155,11 @@ def test_target_masked_tokens(mode, dtype):
     (300, 1, 16 * 2048 - 8, W.BF16),   # more positions than groups: several per group, the last round partial
     (70, 4, 80 * 1024 + 12, W.BF16),   # the same with slices exchanging records
     (2, 3, 19 * 2048 + 4, W.F32),
+    (5, 3, 2049, W.BF16),         # rows at odd addresses, a last vector of one, two and three elements
+    (5, 3, 38 * 2048 + 2, W.BF16),
+    (4, 2, 2048 + 7, W.F32),
+    (4, 2, 19 * 2048 + 2, W.F32),
+    (3, 2, 5, W.F32),             # one vector and one element
     (2, 8, 262144, W.F32),        # more slices than a position may take: the two-read passes
 ])
 def test_single_read_edges(N, K, V, dtype, mode):
