@@ -176,9 +176,8 @@ typedef struct {
                  more than the device holds at once selects the chain, or
                  SPEC_EUNSUPPORTED with SPEC_PATH_SINGLE_READ) */
   int residual_shape; /* chain: how the second pass reads each row's residual step
-                         (0 = chosen by the library from B and V; 1 = one wave
-                         per sub-chunk; 2 = one workgroup per sub-chunk, the
-                         small-batch shape).  Every shape gives the same bits. */
+                         (0 = chosen by the library from the sizes; 1 = one wave
+                         per sub-chunk; 2 = one workgroup per sub-chunk).  Every shape gives the same bits. */
 } spec_launch;
 
 /*

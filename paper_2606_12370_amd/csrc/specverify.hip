@@ -42,11 +42,26 @@ constexpr int kStatVec = 8;
 // V=151936 bf16 177.6 against 179.0 us per call with 4, K=1 88.0 against
 // 90.8; B=1024, V=262144 1074 against 1068)
 constexpr int kPairVec = 2;
-// Pair-pass items below which a launch of residual-step items only gives
-// each one a workgroup (the small-batch launch shape).
-constexpr int64_t kSharedItems = 8192;
-// Residual-step items up to which the pair pass takes them first (about the
-// waves the device holds at once).
+// Pair-pass items up to which each gets a workgroup whose waves share its load
+// steps, two each, issued together.  A wave that takes an item alone waits for
+// eight load steps in turn, which bounds every call that does not fill the
+// device many times over.  Measured, the better order of one wave against
+// one workgroup per item (same bits, us a call, rollout recipe, V = 151936
+// bfloat16, K = 3 with overlaps): B = 1 33.6 / 25.4, B = 4 45.3 / 31.9, B = 16
+// 49.6 / 37.3, B = 64 69.5 / 65.0, B = 128 107.9 / 100.8, B = 256 (14592
+// items) 177.1 / 174.2, B = 512 330.3 / 324.6, B = 1000 (57000) 618.9 / 614.1,
+// but V = 262144, B = 1024 (98304) 1074 / 1085; without overlaps B = 4 43.8 /
+// 31.2, B = 64 65.6 / 56.3, B = 256 142.1 / 130.0, B = 1000 441.3 / 435.6;
+// K = 1 with overlaps B = 256 95.5 / 85.8, B = 1024 273.0 / 263.9; float32 V =
+// 100003, K = 2 with overlaps B = 48 48.9 / 46.5, B = 512 298.3 / 296.4;
+// V = 32000, K = 3 with overlaps B = 16 45.1 / 32.4, B = 2000 297.6 / 296.4.
+constexpr int64_t kSharedItems = 65536;
+// Residual-step items up to which the pair pass takes them first: about the
+// items the device holds at once in each shape (one workgroup per item,
+// residual items first against the pair order: 1216 residual items 65.8 /
+// 66.4 us, 2432 102.3 / 100.8, 4864 178.3 / 174.2; one wave per item: 4864
+// 177.5 / 187.1, 24576 1103 / 1074).
+constexpr int64_t kLongestFirstShared = 1536;
 constexpr int64_t kLongestFirstItems = 8192;
 constexpr int kDiagPairVec = 2;
 // (4 vectors per load step for the diagnostics statistics: 166.5-167.5
@@ -358,26 +373,22 @@ spec_status launch_verify(const sv::VerifyArgs& a, int64_t rows, hipStream_t s, 
   // pair pass: without overlaps only each batch row's residual step is read
   // again.  One wave per item, four per workgroup (measured faster than a
   // grid of what the device holds at once striding over them), or one
-  // workgroup per item for launches whose every item is a residual-step item
-  // (calls without overlaps, and K = 1) with fewer than kSharedItems items.
-  // Measured with warm clocks, the two shapes interleaved (K = 3, V = 151936
-  // bf16 unless noted; us per call): without overlaps B = 64 54.8 against
-  // 64.5, B = 256 136.4 against 137.6, B = 512 247.3 against 245.6, B = 1024
-  // 474.1 against 461.0; K = 1 B = 256 95.4 against 101.0, B = 512 163.7
-  // against 161.6, B = 1024 302.2 against 285.0; with overlaps at K = 3 the
-  // wave shape is faster at every B measured (64: 70.2 against 71.5, 128:
-  // 106.5 against 114.3, 256: 183.2 against 200.3)
+  // workgroup per item for launches of up to kSharedItems items
   const int64_t items = int64_t{a.B} * (a.overlap ? a.K : 1) * a.rows.C;
   const int shape = lc ? lc->residual_shape : 0;
-  const bool residual_only = a.overlap == nullptr || a.K == 1;
-  const int split = shape == 2 || (shape == 0 && residual_only && items < kSharedItems) ? 1 : 0;
-  const int64_t wgs = split ? items : (items + sv::kWaves - 1) / sv::kWaves;
+  const bool split = shape == 2 || (shape == 0 && items <= kSharedItems);
   // residual-step items first while they fit in about one round of what the
   // device holds at once, else the pair order (without overlaps every item
   // is a residual-step item)
-  const int longest_first = (a.overlap == nullptr || int64_t{a.B} * a.rows.C <= kLongestFirstItems) ? 1 : 0;
-  hipLaunchKernelGGL((sv::pair_pass_wave_kernel<E, kStep, kPairVec>), dim3(static_cast<unsigned>(wgs)),
-                     dim3(sv::kThreads), 0, s, a, items, split, longest_first);
+  const int64_t first = int64_t{a.B} * a.rows.C;
+  const int longest_first = (a.overlap == nullptr || first <= (split ? kLongestFirstShared : kLongestFirstItems)) ? 1 : 0;
+  if (split)
+    hipLaunchKernelGGL((sv::pair_pass_wave_kernel<E, kStep, kPairVec, true>), dim3(static_cast<unsigned>(items)),
+                       dim3(sv::kThreads), 0, s, a, items, longest_first);
+  else
+    hipLaunchKernelGGL((sv::pair_pass_wave_kernel<E, kStep, kPairVec, false>),
+                       dim3(static_cast<unsigned>((items + sv::kWaves - 1) / sv::kWaves)), dim3(sv::kThreads), 0, s, a,
+                       items, longest_first);
   // the finish inverts the CDF inside one sub-chunk (kStep tiles, one load step)
   hipLaunchKernelGGL((sv::finish_kernel<E, kStep, kStep>), dim3(static_cast<unsigned>(a.B)), dim3(sv::kThreads), 0,
                      s, a);

@@ -124,6 +124,34 @@ __device__ __forceinline__ void load_span(const typename E::raw* __restrict__ ro
   }
 }
 
+// The two halves of load_span: issue starts the loads, expand waits for them
+// (for a pass that issues several steps' loads first).
+template <class E, int S, int W>
+struct RawSpan {
+  typename E::vec w[S];
+  __device__ __forceinline__ void issue(const typename E::raw* __restrict__ row, int e0, int idx, int V) {
+    if (V < E::EPV) return;  // no whole vector in the row
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const int v0 = e0 + j * W * E::EPV + idx * E::EPV;
+      w[j] = load_vec<E>(row + (v0 + E::EPV <= V ? v0 : 0));
+    }
+  }
+  __device__ __forceinline__ void expand(const typename E::raw* __restrict__ row, int e0, int idx, int V,
+                                         float (&x)[S][E::EPV]) const {
+    constexpr int EPV = E::EPV;
+    const bool none = V < EPV;
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const int v0 = e0 + j * W * EPV + idx * EPV;
+      if (!none) E::widen(w[j], x[j]);
+      if (v0 + EPV > V) {
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) x[j][k] = (v0 + k < V) ? E::one(row + v0 + k) : -INFINITY;
+      }
+    }
+  }
+};
 // Load S tiles (tile0 .. tile0+S-1) of a row, a tile being one vector of each
 // of the workgroup's 256 threads: x[j][k] receives element
 // (tile0 + j) * 256 * EPV + t * EPV + k of the row, t = threadIdx.x.

@@ -9,12 +9,11 @@
 //                 (float64, u q(x) < p(x) with the two gathered logits and
 //                 Philox uniforms); accept length; every output except the
 //                 overlaps and the resampled token.
-//   3 pair_pass   every (target row i, draft row i) pair, one wave (or, for
-//                 small launches of residual steps, one workgroup) per
-//                 sub-chunk: overlap sum min(p, q); for the row's first
-//                 rejected step also the residual sums (residual mass,
-//                 sum (p - q), sum over p > q of q).  Bonus rows are not read
-//                 again, and without an overlap output only each row's
+//   3 pair_pass   every (target row i, draft row i) pair, one workgroup (or
+//                 one wave) per sub-chunk: overlap sum min(p, q); for the
+//                 row's first rejected step also the residual sums (residual
+//                 mass, sum (p - q), sum over p > q of q).  Bonus rows are not
+//                 read again, and without an overlap output only each row's
 //                 residual step is.
 //   4 finish      one workgroup per batch row: overlaps; the normalisation
 //                 correction of the residual; the sub-chunk whose cumulative
@@ -309,15 +308,11 @@ struct StepSums {
 };
 
 template <class E, int S>
-__device__ __forceinline__ StepSums pair_step_sums(const typename E::raw* rt, const typename E::raw* rd, int es,
-                                                   int lane, int V, float s, const RowNorm& nt,
-                                                   const RowNorm& nd, bool need_z, const ResidualRef& rr, float rft,
-                                                   float rfd) {
+__device__ __forceinline__ StepSums pair_step_sums(const float (&xt)[S][E::EPV], const float (&xd)[S][E::EPV], float s,
+                                                   const RowNorm& nt, const RowNorm& nd, bool need_z,
+                                                   const ResidualRef& rr, float rft, float rfd) {
   constexpr int EPV = E::EPV;
   StepSums o = {{0.f, 0.f, 0.f, 0.f}};
-  float xt[S][EPV], xd[S][EPV];
-  load_span<E, S, 64>(rt, es, lane, V, xt);
-  load_span<E, S, 64>(rd, es, lane, V, xd);
   if (need_z) {
 #pragma unroll
     for (int q = 0; q < S; ++q)
@@ -336,6 +331,16 @@ __device__ __forceinline__ StepSums pair_step_sums(const typename E::raw* rt, co
       for (int k = 0; k < EPV; ++k) o.v[0] += overlap_term<E>(xt[q][k], xd[q][k], s, nt, nd, rft, rfd);
   }
   return o;
+}
+template <class E, int S>
+__device__ __forceinline__ StepSums pair_step_sums(const typename E::raw* rt, const typename E::raw* rd, int es,
+                                                   int lane, int V, float s, const RowNorm& nt,
+                                                   const RowNorm& nd, bool need_z, const ResidualRef& rr, float rft,
+                                                   float rfd) {
+  float xt[S][E::EPV], xd[S][E::EPV];
+  load_span<E, S, 64>(rt, es, lane, V, xt);
+  load_span<E, S, 64>(rd, es, lane, V, xd);
+  return pair_step_sums<E, S>(xt, xd, s, nt, nd, need_z, rr, rft, rfd);
 }
 
 // Pass 2 over (pair, sub-chunk) items.  Sub-chunk j covers ST tiles of 256
@@ -356,49 +361,43 @@ __device__ __forceinline__ StepSums pair_step_sums(const typename E::raw* rt, co
 // longest-first order would run a phase of residual items alone, bound by
 // the VALU, before a phase bound by memory, while the pair order mixes them.
 // Two launch shapes:
-//  - split == 0: one wave per item, kWaves items per workgroup;
-//  - split == 1 (small batches, where one wave per item leaves the device
-//    with too few loads in flight and the residual items' serial latency
-//    bounds the launch): one workgroup per item, its kWaves waves sharing
-//    the item's load steps and handing their per-lane step sums to wave 0
+//  - one wave per item, kWaves items per workgroup;
+//  - SPLIT (launches that do not fill the device several times over, where
+//    the serial load steps of an item bound the launch): one workgroup per
+//    item, its kWaves waves sharing the item's load steps, all of a wave's
+//    loads issued together, and handing their per-lane step sums to wave 0
 //    through LDS.
 // Without overlaps only the residual-step items are launched.
 // (The kernel runs each of its waves' items through pair_item, as a
-// wave-stride loop for split == 0; in this form the compiler schedules the
+// wave-stride loop in the first shape; in this form the compiler schedules the
 // item's loads so that the pass runs 3-4 us faster at the B=256 batch, same
 // bits.)
-template <class E, int ST, int S>
-__device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, int split, int longest_first,
-                                          int64_t g_wave);
-template <class E, int ST, int S>
-__global__ __launch_bounds__(kThreads) void pair_pass_wave_kernel(VerifyArgs a, int64_t nitems, int split,
-                                                                  int longest_first) {
-  if (split) {
-    pair_item<E, ST, S>(a, nitems, split, longest_first, -1);
+template <class E, int ST, int S, bool SPLIT>
+__device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, int longest_first, int64_t g_wave);
+template <class E, int ST, int S, bool SPLIT>
+__global__ __launch_bounds__(kThreads) void pair_pass_wave_kernel(VerifyArgs a, int64_t nitems, int longest_first) {
+  if (SPLIT) {
+    pair_item<E, ST, S, true>(a, nitems, longest_first, static_cast<int64_t>(blockIdx.x));
     return;
   }
   const int wave = threadIdx.x >> 6;
   for (int64_t g = static_cast<int64_t>(blockIdx.x) * kWaves + wave; g < nitems;
        g += static_cast<int64_t>(gridDim.x) * kWaves)
-    pair_item<E, ST, S>(a, nitems, split, longest_first, g);
+    pair_item<E, ST, S, false>(a, nitems, longest_first, g);
 }
 
-// One item (split == 0: item g_wave of this wave; split == 1: item blockIdx.x
-// of the whole workgroup).
-template <class E, int ST, int S>
-__device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, int split, int longest_first,
-                                          int64_t g_wave) {
+// Item g of this wave, or (SPLIT) of the whole workgroup.
+template <class E, int ST, int S, bool SPLIT>
+__device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, int longest_first, int64_t g) {
   constexpr int EPV = E::EPV;
   constexpr int WV = ST * (kThreads / 64);
   constexpr int NS = WV / S;  // load steps per sub-chunk
   static_assert(WV % S == 0 && NS % kWaves == 0, "whole load steps per sub-chunk and wave");
-  __shared__ float part[NS][4][64];
+  __shared__ float part[SPLIT ? NS : 1][4][64];
   const RowsDesc& d = a.rows;
   const int C = d.C;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t first = static_cast<int64_t>(a.B) * C;
-  const bool shared_item = split != 0;
-  const int64_t g = shared_item ? static_cast<int64_t>(blockIdx.x) : g_wave;
   if (g >= nitems) return;  // (uniform over a workgroup that shares its item)
   int b, i, j;
   bool need_z;
@@ -443,15 +442,28 @@ __device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, i
   const float rfd = static_cast<float>(static_cast<double>(nd.M) + static_cast<double>(nd.L));
   const int e0 = j * WV * 64 * EPV;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (shared_item) {
+  if constexpr (SPLIT) {
+    // the wave's steps, every load issued before the first is waited for
     constexpr int NW = NS / kWaves;
-#pragma unroll 1
-    for (int st = wave * NW; st < (wave + 1) * NW; ++st) {
-      const int es = e0 + st * S * 64 * EPV;
-      StepSums ps = {{0.f, 0.f, 0.f, 0.f}};
-      if (es < d.V) ps = pair_step_sums<E, S>(rt, rd, es, lane, d.V, s, nt, nd, need_z, rr, rft, rfd);
+    const int st0 = wave * NW;
+    RawSpan<E, S, 64> wt[NW], wd[NW];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) part[st][q][lane] = ps.v[q];
+    for (int q = 0; q < NW; ++q) {
+      wt[q].issue(rt, e0 + (st0 + q) * S * 64 * EPV, lane, d.V);
+      wd[q].issue(rd, e0 + (st0 + q) * S * 64 * EPV, lane, d.V);
+    }
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const int es = e0 + (st0 + q) * S * 64 * EPV;
+      StepSums ps = {{0.f, 0.f, 0.f, 0.f}};
+      if (es < d.V) {
+        float xt[S][EPV], xd[S][EPV];
+        wt[q].expand(rt, es, lane, d.V, xt);
+        wd[q].expand(rd, es, lane, d.V, xd);
+        ps = pair_step_sums<E, S>(xt, xd, s, nt, nd, need_z, rr, rft, rfd);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[st0 + q][v][lane] = ps.v[v];
     }
     __syncthreads();
     if (wave != 0) return;
