@@ -103,7 +103,8 @@ struct KlArgs {
   KlStat* stats;         // [2 N K][SC]
   int SC;                // sub-chunks per row of the statistics pass
   KlNorm* norms;         // [2 N K]
-  KlPart* parts;         // [N K][C]
+  KlPart* parts;         // [N K][PC]
+  int PC;                // chunks per row of kl_pass and kl_grad
   float4* coef;          // [N K]: reverse KL the gradient factor and mu - c; forward KL, CE lam_t - lam_d as hi + lo
   double pair_limit;     // forward KL, CE: |lam_t - lam_d| up to which x is summed pairwise
   double* loss_pos;      // [N]
@@ -500,7 +501,7 @@ __global__ __launch_bounds__(kThreads) void kl_pass_kernel(KlArgs a, int64_t nta
   constexpr int TILE = kThreads * EPV;
   __shared__ RedLds<4> red;
   const RowsDesc& d = a.rows;
-  const int C = d.C, V = d.V, NK = a.N * a.K;
+  const int C = a.PC, V = d.V, NK = a.N * a.K;
   for (int64_t t = blockIdx.x; t < ntasks; t += gridDim.x) {
     const int u = static_cast<int>(t / C), c = static_cast<int>(t - static_cast<int64_t>(t / C) * C);
     int bb;
@@ -540,7 +541,7 @@ __global__ __launch_bounds__(kThreads) void kl_coef_kernel(KlArgs a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = blockIdx.x * kWaves + wave;
   if (n >= a.N) return;
-  const int C = a.rows.C, K = a.K;
+  const int C = a.PC, K = a.K;
   double Ln = 0.0;
   for (int kk = 0; kk < K; ++kk) {
     double se = 0.0, sf = 0.0, w = 0.0;
@@ -607,21 +608,19 @@ __global__ __launch_bounds__(kThreads) void kl_coef_kernel(KlArgs a) {
 // pairwise partition-function ratio of kl_coef.  Reverse KL: scale / (K T)
 // q ln2 ((d - c) - (mu - c)).
 template <class E, int NT, int S, int KIND>
-__global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t ntasks) {
+__global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t nitems, int per_pair) {
   constexpr int EPV = E::EPV;
   constexpr int TILE = kThreads * EPV;
-  // Forward KL / CE: one workgroup per (position, step) pair, its chunks in
-  // turn, since every pair beyond the pair limit leaves at once; reverse
-  // KL: one workgroup per chunk (ntasks of them).
-  constexpr bool kPerPair = KIND != kKlReverse;
+  // One workgroup per chunk, or (per_pair, large forward-KL / CE calls) per
+  // (position, step) pair, its chunks in turn, since every pair beyond the
+  // pair limit leaves at once.
   const RowsDesc& d = a.rows;
-  const int C = d.C, V = d.V, NK = a.N * a.K;
+  const int C = a.PC, V = d.V, NK = a.N * a.K;
   const float gcoef = static_cast<float>(a.scale * static_cast<double>(a.inv_t) / a.K);
-  const int64_t nitems = kPerPair ? static_cast<int64_t>(NK) : ntasks;
   for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int u = kPerPair ? static_cast<int>(it) : static_cast<int>(it / C);
-    const int c0 = kPerPair ? 0 : static_cast<int>(it - static_cast<int64_t>(u) * C);
-    const int c1 = kPerPair ? C : c0 + 1;
+    const int u = per_pair ? static_cast<int>(it) : static_cast<int>(it / C);
+    const int c0 = per_pair ? 0 : static_cast<int>(it - static_cast<int64_t>(u) * C);
+    const int c1 = per_pair ? C : c0 + 1;
     int bb;
     const typename E::raw* rt = row_of<E>(d, u, &bb);
     const typename E::raw* rd = row_of<E>(d, NK + u, &bb);

@@ -568,10 +568,27 @@ spec_status launch_tv(const sv::TvArgs& a, void* res_ws, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
-template <class E, int NT, int KIND>
+// (position, step, 16384-element chunk) tasks of a KL call up to which its
+// passes take chunks of 8192 elements, one workgroup each: a workgroup's load
+// steps follow each other, which bounds calls that do not fill the device many
+// times over.  Measured, 16384 against 8192 elements, us a call with gradient
+// (reverse KL; forward KL gains as much, and the next constant's step on top):
+// N = 8, K = 3, V = 151936 bfloat16 55.9 / 47.4; N = 64, V = 65536 69.8 /
+// 64.9; N = 300, K = 2, V = 50000 float32 173.5 / 163.3; N = 270, K = 3,
+// V = 151936 (8100 tasks) 368.7 / 359.4; N = 2048 2606 / 2626.  Without a
+// gradient: 2400 tasks 101.4 / 98.1, 6000 145.3 / 149.6.
+constexpr int64_t kKlSmallTasks = 8192;
+constexpr int64_t kKlSmallTasksForward = 4096;
+// Tasks beyond which the forward-KL / CE gradient pass takes a workgroup per
+// pair instead of one per chunk (forward KL, K = 3, V = 151936 bfloat16, us a
+// call): N = 200 312 / 229, N = 300 410 / 334, N = 2048 (61440 tasks) 2115 /
+// 2087, N = 6000 (180000) 6080 / 6155.
+constexpr int64_t kKlPairTasks = 100000;
+
+template <class E, int KIND, int CHUNK>
 spec_status launch_kl(const sv::KlArgs& a, hipStream_t s) {
   const int64_t units = int64_t{a.N} * a.K;
-  const int C = a.rows.C;
+  const int C = a.PC;
   // statistics per sub-chunk, one wave each; float32 logits carry their
   // exponents beyond float32 (their tolerance is 200 times tighter)
   const int64_t nsub = 2 * units * a.SC;
@@ -596,36 +613,37 @@ spec_status launch_kl(const sv::KlArgs& a, hipStream_t s) {
   // (6.8 against 7.2 ms)
   using G = typename GradElem<E>::type;
   using P = typename std::conditional<KIND == sv::kKlReverse, E, G>::type;
-  constexpr int NTP = kChunkElems / (sv::kThreads * P::EPV);
-  constexpr int NTG = kChunkElems / (sv::kThreads * G::EPV);
   // tiles per load step: 2 for the forward-KL / CE pass with the pairwise x
   // (24.5-24.8 against 25.6-25.8 ms per call), 4 for its loop body without
   // x (forward KL 21.2-21.4 against 22.4-22.7 ms; 8: 21.0-21.4), 2 for the
   // reverse-KL pass (21.1-21.2 against 21.3-21.7 ms with 4, 22.5 with 8)
   constexpr int SP = 2;
   constexpr int SPN = KIND == sv::kKlReverse ? 2 : kStep;
-  void (*kp)(sv::KlArgs, int64_t) = sv::kl_pass_kernel<P, NTP, SP, SPN, KIND>;
+  void (*kp)(sv::KlArgs, int64_t) = sv::kl_pass_kernel<P, CHUNK / (sv::kThreads * P::EPV), SP, SPN, KIND>;
   // one workgroup per task (measured faster than a resident grid: reverse KL 22.8 -> 21.2 ms per call)
   hipLaunchKernelGGL(kp, dim3(static_cast<unsigned>(units * C)), dim3(sv::kThreads), 0, s, a,
                      units * C);
   hipLaunchKernelGGL(sv::kl_coef_kernel, dim3(static_cast<unsigned>((a.N + sv::kWaves - 1) / sv::kWaves)),
                      dim3(sv::kThreads), 0, s, a);
   if (a.grad) {
-    // reverse KL: one workgroup per chunk; forward KL / CE: one per pair (only
-    // the pairs within the pair limit are left to write)
-    void (*kg)(sv::KlArgs, int64_t) = sv::kl_grad_kernel<G, NTG, kStep, KIND>;
-    const int64_t grid = KIND == sv::kKlReverse ? units * C : units;
-    hipLaunchKernelGGL(kg, dim3(static_cast<unsigned>(grid)), dim3(sv::kThreads), 0, s, a, units * C);
+    // one workgroup per chunk; forward KL / CE (only the pairs within the pair
+    // limit are left to write): one per pair in the largest calls, where the
+    // workgroups that leave at once would cost more than the last one that
+    // walks its pair alone (100 us at V = 151936)
+    void (*kg)(sv::KlArgs, int64_t, int) = sv::kl_grad_kernel<G, CHUNK / (sv::kThreads * G::EPV), kStep, KIND>;
+    const int per_pair = KIND != sv::kKlReverse && units * C > kKlPairTasks ? 1 : 0;
+    const int64_t grid = per_pair ? units : units * C;
+    hipLaunchKernelGGL(kg, dim3(static_cast<unsigned>(grid)), dim3(sv::kThreads), 0, s, a, grid, per_pair);
   }
   hipLaunchKernelGGL(sv::kl_loss_kernel, dim3(1), dim3(sv::kThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
-template <class E, int NT>
+template <class E, int CHUNK>
 spec_status launch_kl_kind(const sv::KlArgs& a, hipStream_t s) {
-  if (a.kind == sv::kKlForward) return launch_kl<E, NT, sv::kKlForward>(a, s);
-  if (a.kind == sv::kKlCe) return launch_kl<E, NT, sv::kKlCe>(a, s);
-  return launch_kl<E, NT, sv::kKlReverse>(a, s);
+  if (a.kind == sv::kKlForward) return launch_kl<E, sv::kKlForward, CHUNK>(a, s);
+  if (a.kind == sv::kKlCe) return launch_kl<E, sv::kKlCe, CHUNK>(a, s);
+  return launch_kl<E, sv::kKlReverse, CHUNK>(a, s);
 }
 
 // Target-only verification and the sampler keep statistics per sub-chunk
@@ -1118,7 +1136,12 @@ spec_status spec_kl_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, 
   a.stats = reinterpret_cast<sv::KlStat*>(ws + L.stats);
   a.SC = sub_chunks(V, dtype);
   a.norms = reinterpret_cast<sv::KlNorm*>(ws + L.norms);
-  a.parts = reinterpret_cast<sv::KlPart*>(ws + L.parts);
+  // the partial sums per chunk; twice as many fit in the statistics' place,
+  // which nothing reads once the pass runs
+  const bool small = int64_t{N} * K * g.C <= (grad_draft ? kKlSmallTasks : kKlSmallTasksForward);
+  const int chunk = small ? kChunkElems / 2 : kChunkElems;
+  a.PC = (V + chunk - 1) / chunk;
+  a.parts = reinterpret_cast<sv::KlPart*>(ws + (small ? L.stats : L.parts));
   a.coef = reinterpret_cast<float4*>(ws + L.coef);
   a.loss_pos = reinterpret_cast<double*>(ws + L.loss);
   // lam_t - lam_d = log2(max q / max p); beyond the limit the separately
@@ -1127,7 +1150,9 @@ spec_status spec_kl_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, 
   // largest |q - p|, far inside the tolerances (2e-3, 1e-5)
   a.pair_limit = dtype == SPEC_BF16 ? 1.0 / 64 : 0.5;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return dtype == SPEC_BF16 ? launch_kl_kind<BF16, kNtBf16>(a, s) : launch_kl_kind<F32, kNtF32>(a, s);
+  if (small)
+    return dtype == SPEC_BF16 ? launch_kl_kind<BF16, kChunkElems / 2>(a, s) : launch_kl_kind<F32, kChunkElems / 2>(a, s);
+  return dtype == SPEC_BF16 ? launch_kl_kind<BF16, kChunkElems>(a, s) : launch_kl_kind<F32, kChunkElems>(a, s);
 }
 
 }  // extern "C"

@@ -199,3 +199,34 @@ def test_target_masked_tokens_forward_and_ce(dtype):
         loss, ps, grad, ref = run_case(d, kind, 0.9)
         assert np.all(np.isfinite(ref["grad"])) and np.all(np.isfinite(ref["per_step"]))
         print(kind, dtype, compare_kl(loss, ps, grad, ref, dtype))
+
+
+@pytest.mark.parametrize("kind", ["forward", "ce", "reverse"])
+@pytest.mark.parametrize("N,K,V,dtype", [
+    (256, 2, 16384 * 15 + 9, W.BF16),   # the most tasks with the smaller chunks (8192), a last chunk of nine
+    (257, 2, 16384 * 15 + 9, W.BF16),   # the larger chunks, gradient pass by chunk
+    (1200, 4, 16385, W.F32),            # the same, two chunks a row
+    (50100, 2, 128, W.BF16),            # gradient pass by pair
+])
+def test_chunk_rules(N, K, V, dtype, kind):
+    """Either side of the sizes where the passes change their chunks and the
+    gradient pass its workgroups: sampled positions against the oracle (some
+    with a draft so close to the target that the gradient pass writes them),
+    and a forward-only call."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + V)
+    td = torch.bfloat16 if dtype == W.BF16 else torch.float32
+    tgt = (3 * torch.randn((N, K, V), device="cuda", generator=g)).to(td)
+    noise = torch.where(torch.arange(N, device="cuda") % 3 == 0, 0.003, 1.0)[:, None, None]
+    drf = (tgt.float() + noise * torch.randn((N, K, V), device="cuda", generator=g)).to(td)
+    loss, ps, grad = binding.kl_loss_fwd_bwd(tgt, drf, 0.9, kind, 0.5)
+    loss2, ps2, _ = binding.kl_loss_fwd_bwd(tgt, drf, 0.9, kind, 0.5, want_grad=False)
+    torch.cuda.synchronize()
+    pos = np.array([0, 1, N // 2, N - 3, N - 2, N - 1])
+    pi = torch.as_tensor(pos, device="cuda")
+    ref = kl_ref(host_logits(tgt[pi], dtype), host_logits(drf[pi], dtype), float(np.float32(0.9)), KINDS[kind], 0.5)
+    compare_kl(loss, ps, grad, ref, dtype, positions=pos, loss_exact=False)
+    compare_kl(loss2, ps2, None, ref, dtype, positions=pos, loss_exact=False)
+    total = 0.5 * float(ps.double().sum()) / K
+    for x in (loss, loss2):
+        assert abs(float(x) - total) <= 1e-5 * abs(total) + 1e-6 * N
