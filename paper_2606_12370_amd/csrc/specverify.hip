@@ -665,8 +665,8 @@ spec_status launch_sample(const sv::SampleArgs& a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
-// Diagnostics per sub-chunk of kStep tiles, one wave per sub-chunk in both
-// streaming passes.
+// Diagnostics per sub-chunk of kStep tiles, one wave per sub-chunk in the
+// statistics, one workgroup in the pair pass.
 template <class E>
 spec_status launch_diag(const sv::DiagArgs& a, hipStream_t s) {
   const int C = a.rows.C;
@@ -677,9 +677,8 @@ spec_status launch_diag(const sv::DiagArgs& a, hipStream_t s) {
                      a.rows, const_cast<sv::DiagStat*>(a.stats), nsub);
   hipLaunchKernelGGL(sv::diag_norm_kernel, dim3(static_cast<unsigned>((2 * units + sv::kWaves - 1) / sv::kWaves)),
                      dim3(sv::kThreads), 0, s, a.stats, static_cast<int>(2 * units), C, a.norms, a.info);
-  hipLaunchKernelGGL((sv::diag_pair_wave_kernel<E, kStep, kDiagPairVec>),
-                     dim3(static_cast<unsigned>((units * C + sv::kWaves - 1) / sv::kWaves)), dim3(sv::kThreads), 0,
-                     s, a, units * C);
+  hipLaunchKernelGGL((sv::diag_pair_kernel<E, kStep, kDiagPairVec>), dim3(static_cast<unsigned>(units * C)),
+                     dim3(sv::kThreads), 0, s, a);
   hipLaunchKernelGGL((sv::diag_finish_kernel<E>), dim3(static_cast<unsigned>((units + sv::kWaves - 1) / sv::kWaves)),
                      dim3(sv::kThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;

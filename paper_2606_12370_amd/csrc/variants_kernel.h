@@ -14,7 +14,7 @@
 //     sum min(p_i, q_i) split into sum_{p>q} q and sum_{q>=p} p.  Four
 //     launches: diag_stats (one wave per sub-chunk: max reference, exp2 sum,
 //     the entropy moment, largest logit and its first index), diag_norm (one
-//     wave per row), diag_pair (one wave per pair sub-chunk), diag_finish
+//     wave per row), diag_pair (one workgroup per pair sub-chunk), diag_finish
 //     (one wave per step).
 #pragma once
 
@@ -426,38 +426,50 @@ __global__ __launch_bounds__(kThreads) void diag_stats_wave_kernel(RowsDesc d, D
   }
 }
 
-// Split overlap sums, one wave per (pair, sub-chunk) item: item g = u * C + j
-// is sub-chunk j of pair u (target row u, draft row B*K + u of the
-// diagnostics row layout); gt = sum over p > q of q, ge = sum over q >= p of
-// p, S vectors of each row per lane per load step, then float64 wave sums.
-// One exponential per element pair: with x = log2 p and y = log2 q,
-// 2^min(x, y) is q where x > y and p elsewhere, so x > y routes it.
+// Split overlap sums of one (pair, sub-chunk) item: item g = u * C + j is
+// sub-chunk j of pair u (target row u, draft row B*K + u of the diagnostics
+// row layout); gt = sum over p > q of q, ge = sum over q >= p of p, S vectors
+// of each row per lane per load step.  One exponential per element pair: with
+// x = log2 p and y = log2 q, 2^min(x, y) is q where x > y and p elsewhere, so
+// x > y routes it.  One workgroup per item: its waves share the load steps,
+// all of a wave's loads issued before the first is waited for, float64 sums
+// over the waves.  (One wave per item, its eight load steps in turn, against
+// this, us a call at K = 3, V = 151936 bfloat16: B = 8 40.5 / 32.5, B = 64
+// 62.8 / 56.3, B = 256 167.1 / 162.3, B = 700 422.5 / 417.6; four vectors per
+// load step 163.5 at B = 256.)
 template <class E, int ST, int S>
-__global__ __launch_bounds__(kThreads) void diag_pair_wave_kernel(DiagArgs a, int64_t nitems) {
+__global__ __launch_bounds__(kThreads) void diag_pair_kernel(DiagArgs a) {
   constexpr int EPV = E::EPV;
   constexpr int WV = ST * (kThreads / 64);
-  static_assert(WV % S == 0, "whole load steps per sub-chunk");
+  constexpr int NW = WV / S / kWaves;  // load steps per wave
+  static_assert(WV % (S * kWaves) == 0, "whole load steps per wave");
+  __shared__ double part[kWaves][2];
   const RowsDesc& d = a.rows;
   const int C = d.C, BK = a.B * a.K;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t g = static_cast<int64_t>(blockIdx.x) * kWaves + wave;
-  if (g >= nitems) return;  // the whole wave leaves: nothing below synchronises the workgroup
+  const int64_t g = static_cast<int64_t>(blockIdx.x);
   const int u = static_cast<int>(g / C), j = static_cast<int>(g - static_cast<int64_t>(g / C) * C);
   int b;
   const typename E::raw* rt = row_of<E>(d, u, &b);
   const typename E::raw* rd = row_of<E>(d, BK + u, &b);
+  const int e0 = (j * WV + wave * NW * S) * 64 * EPV;
+  RawSpan<E, S, 64> wt[NW], wd[NW];
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    wt[q].issue(rt, e0 + q * S * 64 * EPV, lane, d.V);
+    wd[q].issue(rd, e0 + q * S * 64 * EPV, lane, d.V);
+  }
   const float T = temperature_of(d, b);
   const float s = temperature_ok(T) ? scale_of(T) : 1.0f;
   const RowNorm nt = a.norms[u], nd = a.norms[BK + u];
-  const int e0 = j * WV * 64 * EPV;
   float gt = 0.f, ge = 0.f;
 #pragma unroll
-  for (int st = 0; st < WV / S; ++st) {
-    const int es = e0 + st * S * 64 * EPV;
+  for (int q = 0; q < NW; ++q) {
+    const int es = e0 + q * S * 64 * EPV;
     if (es >= d.V) break;  // wave-uniform: the row's last sub-chunk may be short
     float xt[S][EPV], xd[S][EPV];
-    load_span<E, S, 64>(rt, es, lane, d.V, xt);
-    load_span<E, S, 64>(rd, es, lane, d.V, xd);
+    wt[q].expand(rt, es, lane, d.V, xt);
+    wd[q].expand(rd, es, lane, d.V, xd);
 #pragma unroll
     for (int i = 0; i < S; ++i)
 #pragma unroll
@@ -472,8 +484,18 @@ __global__ __launch_bounds__(kThreads) void diag_pair_wave_kernel(DiagArgs a, in
   const double vgt = wave_sum(static_cast<double>(gt));
   const double vge = wave_sum(static_cast<double>(ge));
   if (lane == 0) {
+    part[wave][0] = vgt;
+    part[wave][1] = vge;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
     DiagPair o;
-    o.gt = vgt; o.ge = vge;
+    o.gt = 0.0;
+    o.ge = 0.0;
+    for (int w = 0; w < kWaves; ++w) {
+      o.gt += part[w][0];
+      o.ge += part[w][1];
+    }
     a.pairs[g] = o;
   }
 }
