@@ -194,3 +194,49 @@ def test_single_read_data_errors():
         torch.cuda.synchronize()
         assert torch.isnan(loss).all() and torch.isnan(ov[1, 0]) and torch.isnan(grad[1]).all()
         assert torch.isfinite(grad[0]).all() and torch.isfinite(grad[2]).all() and torch.isfinite(ov[0]).all()
+
+
+def test_single_read_graph_replays():
+    """A captured gradient call gives the eager results on every replay (the
+    launches reset their own counters and records), with eager calls and other
+    inputs in between."""
+    N, K, V = 70, 2, 90000
+    d = [W.tv_inputs_numpy(N, K, V, W.BF16, 40 + i) for i in range(2)]
+    dev = [device_inputs(x) for x in d]
+    eager = [binding.tv_loss_fwd_bwd(t, q, 1.0, "e2e", 0.5) for t, q in dev]
+    tgt, drf = dev[0][0].clone(), dev[0][1].clone()
+    ws = torch.empty(binding.tv_workspace_size(N, K, V), dtype=torch.uint8, device="cuda")
+    grad = torch.empty((N, K, V), device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        loss, ov, _ = binding.tv_loss_fwd_bwd(tgt, drf, 1.0, "e2e", 0.5, ws=ws, grad_out=grad)
+    for i in (0, 1, 0, 0, 1):
+        tgt.copy_(dev[i][0])
+        drf.copy_(dev[i][1])
+        grad.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, want in zip((loss, ov, grad), eager[i]):
+            assert torch.equal(got, want)
+        binding.tv_loss_fwd_bwd(*dev[1 - i], 1.0, "e2e", 0.5)
+
+
+def test_single_read_two_streams():
+    """Calls on two streams at once, each with its own workspace: whichever
+    workgroups the device holds, every group finishes, with the same bits."""
+    N, K, V = 400, 3, 100000
+    d = W.tv_inputs_torch(N, K, V, W.BF16, 51, chunk=64)
+    want = binding.tv_loss_fwd_bwd(d["target"], d["draft"], 1.0, "prod", 1.0)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    ws = [torch.empty(binding.tv_workspace_size(N, K, V), dtype=torch.uint8, device="cuda") for _ in streams]
+    outs = [[], []]
+    for _ in range(3):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                outs[i].append(binding.tv_loss_fwd_bwd(d["target"], d["draft"], 1.0, "prod", 1.0, ws=ws[i]))
+    torch.cuda.synchronize()
+    for o in outs[0] + outs[1]:
+        for got, ref in zip(o, want):
+            assert torch.equal(got, ref)
