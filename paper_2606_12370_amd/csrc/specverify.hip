@@ -56,6 +56,13 @@ constexpr int kPairVec = 2;
 // 100003, K = 2 with overlaps B = 48 48.9 / 46.5, B = 512 298.3 / 296.4;
 // V = 32000, K = 3 with overlaps B = 16 45.1 / 32.4, B = 2000 297.6 / 296.4.
 constexpr int64_t kSharedItems = 65536;
+// Items up to which the decisions are taken inside the pair pass, by every
+// workgroup for itself (a launch fewer against the repeated work; K = 3, V =
+// 151936 bfloat16, us a call, two launches / one): without overlaps B = 1
+// 24.0 / 20.9, B = 8 (152 items) 31.7 / 29.5, B = 32 (608) 43.3 / 40.7, B = 64
+// (1216) 56.7 / 56.2, B = 128 80.9 / 86.4; with overlaps B = 4 (228) 31.3 /
+// 28.7, B = 16 (912) 37.2 / 37.0, B = 32 (1824) 47.1 / 52.1.
+constexpr int64_t kDecidePairItems = 768;
 // Residual-step items up to which the pair pass takes them first: about the
 // items the device holds at once in each shape (one workgroup per item,
 // residual items first against the pair order: 1216 residual items 65.8 /
@@ -369,13 +376,20 @@ spec_status launch_verify(const sv::VerifyArgs& a, int64_t rows, hipStream_t s, 
   }
   // statistics and pair sums per sub-chunk of kStep tiles, one wave per sub-chunk
   launch_stats_wave<E>(a.rows, const_cast<sv::RowStat*>(a.stats), rows, s);
+  const int64_t items = int64_t{a.B} * (a.overlap ? a.K : 1) * a.rows.C;
+  const int shape = lc ? lc->residual_shape : 0;
+  if (shape == 0 && items <= kDecidePairItems) {
+    hipLaunchKernelGGL((sv::decide_pair_kernel<E, kStep, kPairVec>), dim3(static_cast<unsigned>(items)),
+                       dim3(sv::kThreads), 0, s, a, static_cast<int>(items / a.B));
+    hipLaunchKernelGGL((sv::finish_kernel<E, kStep, kStep>), dim3(static_cast<unsigned>(a.B)), dim3(sv::kThreads), 0,
+                       s, a);
+    return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
+  }
   hipLaunchKernelGGL((sv::decide_kernel<E>), dim3(static_cast<unsigned>(a.B)), dim3(sv::kThreads), 0, s, a);
   // pair pass: without overlaps only each batch row's residual step is read
   // again.  One wave per item, four per workgroup (measured faster than a
   // grid of what the device holds at once striding over them), or one
   // workgroup per item for launches of up to kSharedItems items
-  const int64_t items = int64_t{a.B} * (a.overlap ? a.K : 1) * a.rows.C;
-  const int shape = lc ? lc->residual_shape : 0;
   const bool split = shape == 2 || (shape == 0 && items <= kSharedItems);
   // residual-step items first while they fit in about one round of what the
   // device holds at once, else the pair order (without overlaps every item

@@ -1,6 +1,6 @@
 // verify_kernel.h — chain rejection-sampling verification (paper Sec. 2.2,
-// Eq. reject_sample; App. G.1, Alg. rs_multinomial) in four launches that
-// never wait on each other inside a launch:
+// Eq. reject_sample; App. G.1, Alg. rs_multinomial) in four launches (2
+// and 3 are one in small calls) that never wait on each other inside a launch:
 //
 //   1 row_stats   (sv_device.h) every target and draft row, one wave per
 //                 sub-chunk: per-sub-chunk (max reference, exp2 sum).
@@ -217,20 +217,13 @@ __device__ int decide_wave(const VerifyArgs& a, int b, const DecideShared& sh, c
   return n;
 }
 
-// Row normalisers and accept decisions, one workgroup per batch row: every
-// wave combines statistics of its rows, then wave 0 alone decides.
-template <class E>
-__global__ __launch_bounds__(kThreads) void decide_kernel(VerifyArgs a) {
-  __shared__ DecideShared sh;
-  const RowsDesc& d = a.rows;
-  const int K = a.K, C = d.C;
-  const int b = blockIdx.x;
+// The 2K+1 row normalisers of batch row b into sh, whole workgroup: one wave
+// per row, a wave's rows combined two at a time so that their loads are in
+// flight at once (row j < K+1: target row j; row K+1+i: draft row i).  With
+// `store` they also go to a.norms.
+__device__ __forceinline__ void batch_row_norms(const VerifyArgs& a, int b, bool store, DecideShared& sh) {
+  const int K = a.K, C = a.rows.C, R = 2 * K + 1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  DraftGather gx{0, 0.f, 0.f, 0.0};
-  if (static_cast<int>(threadIdx.x) < K) gx = gather_draft<E>(a, b, threadIdx.x);
-  // row j < K+1: target row j; row K+1+i: draft row i (one wave per row, the
-  // rows of a wave combined together so that their loads are in flight at once)
-  const int R = 2 * K + 1;
   for (int j = wave; j < R; j += 2 * kWaves) {
     const int j2 = j + kWaves;
     const int r1 = j <= K ? target_row(a, b, j) : draft_row(a, b, j - K - 1);
@@ -242,17 +235,29 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(VerifyArgs a) {
     if (lane == 0) {
       const RowNorm n1 = make_norm(M1, D1);
       sh.nrm[j] = n1;
-      a.norms[r1] = n1;
+      if (store) a.norms[r1] = n1;
       if (j2 < R) {
         const RowNorm n2 = make_norm(M2, D2);
         sh.nrm[j2] = n2;
-        a.norms[r2] = n2;
+        if (store) a.norms[r2] = n2;
       }
     }
   }
+}
+
+// Row normalisers and accept decisions, one workgroup per batch row: every
+// wave combines statistics of its rows, then wave 0 alone decides.
+template <class E>
+__global__ __launch_bounds__(kThreads) void decide_kernel(VerifyArgs a) {
+  __shared__ DecideShared sh;
+  const int b = blockIdx.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  DraftGather gx{0, 0.f, 0.f, 0.0};
+  if (static_cast<int>(threadIdx.x) < a.K) gx = gather_draft<E>(a, b, threadIdx.x);
+  batch_row_norms(a, b, true, sh);
   __syncthreads();
   if (wave != 0) return;  // the decision is one wave's work
-  const int n = decide_wave<E>(a, b, sh, gx, temperature_of(d, b));
+  const int n = decide_wave<E>(a, b, sh, gx, temperature_of(a.rows, b));
   if (lane == 0) a.decision[b] = n;
 }
 
@@ -498,6 +503,97 @@ __device__ __forceinline__ void pair_item(const VerifyArgs& a, int64_t nitems, i
   o.Sd = need_z ? wave_sum(acc[2]) : 0.0;
   o.Qg = need_z ? wave_sum(acc[3]) : 0.0;
   if (lane == 0) a.pairs[(static_cast<int64_t>(b) * a.K + i) * C + j] = o;
+}
+
+// decide and the pair pass in one launch, for small calls: a launch costs about
+// 3 us and a gap of 1 however little it does.  One workgroup per item, `per` of
+// them a batch row (item i * C + j: step i, sub-chunk j; without overlaps
+// sub-chunk j of the residual step); each forms the row's normalisers and its
+// accept decisions itself, with the item's loads on their way where the step
+// is known before, and the row's first workgroup writes them.  Same sums in
+// the same order as decide_kernel and the pair pass with one workgroup per
+// item.
+template <class E, int ST, int S>
+__global__ __launch_bounds__(kThreads) void decide_pair_kernel(VerifyArgs a, int per) {
+  constexpr int EPV = E::EPV;
+  constexpr int WV = ST * (kThreads / 64);
+  constexpr int NS = WV / S, NW = NS / kWaves;
+  __shared__ float part[NS][4][64];
+  __shared__ DecideShared dec;
+  __shared__ int n_sh;
+  const RowsDesc& d = a.rows;
+  const int K = a.K, C = d.C, V = d.V;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int b = static_cast<int>(blockIdx.x) / per, it = static_cast<int>(blockIdx.x) - b * per;
+  const bool first = it == 0;
+  int i = a.overlap ? it / C : 0;
+  const int j = a.overlap ? it - i * C : it;
+  const int e0 = (j * WV + wave * NW * S) * 64 * EPV;
+  int bb;
+  const typename E::raw* rt = row_of<E>(d, target_row(a, b, i), &bb);
+  const typename E::raw* rd = row_of<E>(d, draft_row(a, b, i), &bb);
+  RawSpan<E, S, 64> wt[NW], wd[NW];
+  auto issue = [&]() {
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      wt[q].issue(rt, e0 + q * S * 64 * EPV, lane, V);
+      wd[q].issue(rd, e0 + q * S * 64 * EPV, lane, V);
+    }
+  };
+  if (a.overlap) issue();
+  DraftGather gx{0, 0.f, 0.f, 0.0};
+  if (static_cast<int>(threadIdx.x) < K) gx = gather_draft<E>(a, b, threadIdx.x);
+  batch_row_norms(a, b, first, dec);
+  __syncthreads();
+  if (wave == 0) {
+    const int n = decide_wave<E>(a, b, dec, gx, temperature_of(d, b), first);
+    if (lane == 0) {
+      n_sh = n;
+      if (first) a.decision[b] = n;
+    }
+  }
+  __syncthreads();
+  const int n = n_sh;
+  if (n < 0) return;  // data error: every output of the row is written
+  if (!a.overlap) {
+    if (n >= K) return;  // no residual step
+    i = n;
+    rt = row_of<E>(d, target_row(a, b, i), &bb);
+    rd = row_of<E>(d, draft_row(a, b, i), &bb);
+    issue();
+  }
+  const bool need_z = i == n;
+  const float s = scale_of(temperature_of(d, b));
+  const RowNorm nt = dec.nrm[i], nd = dec.nrm[K + 1 + i];
+  const ResidualRef rr = need_z ? residual_ref(nt, nd, 0.0) : kNoResidual;
+  const float rft = static_cast<float>(static_cast<double>(nt.M) + static_cast<double>(nt.L));
+  const float rfd = static_cast<float>(static_cast<double>(nd.M) + static_cast<double>(nd.L));
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    const int es = e0 + q * S * 64 * EPV;
+    StepSums ps = {{0.f, 0.f, 0.f, 0.f}};
+    if (es < V) {
+      float xt[S][EPV], xd[S][EPV];
+      wt[q].expand(rt, es, lane, V, xt);
+      wd[q].expand(rd, es, lane, V, xd);
+      ps = pair_step_sums<E, S>(xt, xd, s, nt, nd, need_z, rr, rft, rfd);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wave * NW + q][v][lane] = ps.v[v];
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int st = 0; st < NS; ++st)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] += static_cast<double>(part[st][v][lane]);
+  PairStat o;
+  o.alpha = wave_sum(acc[0]);
+  o.Z = need_z ? wave_sum(acc[1]) : 0.0;
+  o.Sd = need_z ? wave_sum(acc[2]) : 0.0;
+  o.Qg = need_z ? wave_sum(acc[3]) : 0.0;
+  if (lane == 0) a.pairs[(static_cast<int64_t>(b) * K + i) * C + j] = o;
 }
 
 // Residual (or target) mass of the EPV elements of one thread's vector;

@@ -390,3 +390,13 @@ def test_single_read_unsupported_shapes_fall_back_or_refuse():
     compare_verify(out, ref, W.BF16)
     with pytest.raises(binding.SpecError):
         binding.verify(tgt, drf, ids, T, 1, 2, path="single_read")
+
+
+@pytest.mark.parametrize("dtype,B,K,V", [(W.BF16, 256, 3, 8192), (W.BF16, 257, 3, 8192),   # 768 and 771 items
+                                         (W.F32, 1, 1, 1), (W.BF16, 3, 8, 5), (W.F32, 2, 8, 4096 * 65 + 3),
+                                         (W.BF16, 96, 8, 8191)])
+def test_decide_in_the_pair_pass(dtype, B, K, V):
+    """Small calls take their decisions inside the pair pass: the same bits as
+    the launches apart, either side of the limit, for more rows than waves and
+    more sub-chunks than lanes."""
+    test_residual_shapes_give_identical_bits(dtype, B, K, V, "near" if B % 2 else "rollout_t")
