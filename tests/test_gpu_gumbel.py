@@ -245,3 +245,36 @@ def test_verify_scan_parts_without_residual_mass(V):
     ref = verify_gumbel_ref(tgt.astype(np.float64), drf.astype(np.float64), ids, T.astype(np.float64), 4, 1)
     assert (ref["accept_len"] < K).sum() >= B // 4  # rejections to look at
     print(compare_verify_gumbel(out, ref, W.F32))
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("V", [5, 2049, 40000])
+def test_sampler_overflowing_scale(V, dtype):
+    """Finite logits whose z / T overflows float32 (a token forced with the
+    largest finite value; a tiny temperature) are no data error: the row's
+    token is that of the oracle.  NaN and +inf logits stay one at any T."""
+    R = 12
+    top = float(np.finfo(np.float32).max) if dtype == W.F32 else float(np.float32(2.0 ** 128 - 2.0 ** 120))
+    rng = np.random.default_rng(V)
+    z = -np.abs(rng.standard_normal((R, V))).astype(np.float32) - 1.0
+    T = np.ones(R, np.float32)
+    z[0, V - 1] = top
+    z[1, 0] = top
+    z[2, V // 2], T[2] = top, 0.25
+    z[3, V // 2], T[3] = top, 20.0                 # no overflow
+    z[4, V // 3], T[4] = 300.0, 1e-37              # ordinary logits, a tiny temperature
+    z[5, V // 3], T[5] = 300.0, 1e-37
+    z[5, V - 1] = np.nan
+    z[6, V // 3], T[6] = 300.0, 1e-37
+    z[6, 0] = np.inf
+    z[7, V - 1], z[7, 1] = top, np.nan
+    z[8, V - 1], z[8, 1] = top, np.inf
+    z[9, V - 1], z[9, : V // 2] = top, -np.inf
+    z[10, : V - 1], z[10, V - 1] = -np.inf, top
+    d = W.f32_to_bf16_bits(z) if dtype == W.BF16 else z
+    lg = torch.from_numpy(d.view(np.int16)).cuda().view(torch.bfloat16) if dtype == W.BF16 else torch.from_numpy(d).cuda()
+    out = binding.sample_gumbel(lg, torch.from_numpy(T).cuda(), seed=21, offset=2)["tokens"]
+    torch.cuda.synchronize()
+    ref = sample_gumbel_ref(W.to_float64(d, dtype), T.astype(np.float64), 21, 2)
+    assert ref["token"][0] == V - 1 and ref["token"][1] == 0 and (ref["token"][5:9] == -1).all()
+    compare_sample_gumbel(out, ref)
