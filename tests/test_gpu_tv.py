@@ -184,6 +184,36 @@ def test_single_read_edges(N, K, V, dtype, mode):
     assert abs(float(a[0]) - total) <= 1e-5 * abs(total) + 1e-6 * N * K
 
 
+@pytest.mark.parametrize("mode", ["e2e", "prod", "per_step"])
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("V,first,count,masked", [
+    (2048, 0, 4, False), (2052, 2048, 4, False),    # every logit one thread holds
+    (40000, 0, 10240, False),                       # every logit of its first tiles
+    (40000, 123, 1, True), (200000, 199999, 1, True),   # one NaN in a row masked but for a few tokens
+])
+@pytest.mark.parametrize("which", ["target", "draft"])
+def test_single_read_nan_anywhere(which, V, first, count, masked, dtype, mode):
+    """NaN logits wherever they stand, also where a thread holds nothing else:
+    NaN in the position's loss, in the step's overlap and all of its gradient."""
+    N, K = 3, 2
+    d = W.tv_inputs_numpy(N, K, V, W.F32, 8)
+    if masked:
+        for x in (d["target"], d["draft"]):
+            x[1, 0, : V - V // 4] = -np.inf
+            if first >= V - V // 4:
+                x[1, 0, V // 2:] = -np.inf
+                x[1, 0, : 3000] = 0.5
+    d[which][1, 0, first:first + count] = np.nan
+    cast = torch.bfloat16 if dtype == W.BF16 else torch.float32
+    tgt, drf = (torch.from_numpy(d[n]).cuda().to(cast) for n in ("target", "draft"))
+    loss, ov, grad = binding.tv_loss_fwd_bwd(tgt, drf, 1.0, mode, 1.0)
+    torch.cuda.synchronize()
+    assert torch.isnan(loss).all() and torch.isnan(ov[1, 0]) and torch.isnan(grad[1, 0]).all()
+    assert torch.isfinite(ov[0]).all() and torch.isfinite(ov[2]).all() and torch.isfinite(ov[1, 1])
+    assert torch.isfinite(grad[0]).all() and torch.isfinite(grad[2]).all()
+    assert torch.isnan(grad[1, 1]).all() if mode != "per_step" else torch.isfinite(grad[1, 1]).all()
+
+
 def test_single_read_data_errors():
     """NaN or infinite logits make that position's loss and gradient NaN."""
     for bad in (np.nan, np.inf):
