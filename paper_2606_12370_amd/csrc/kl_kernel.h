@@ -393,7 +393,8 @@ template <class E>
 __device__ __forceinline__ float kl_fwd_grad(float e, float f, float dl, const KlNorm& nt, const KlNorm& nd,
                                              float gcoef) {
   const float pe = e * nt.invD, qf = f * nd.invD;
-  const float mx = fmaxf(pe, qf);
+  // keeps NaN: a normaliser that is NaN makes every element of the row NaN
+  const float mx = __builtin_elementwise_maximum(pe, qf);
   const float g = kl_absdiff<E>(mx, fminf(pe, qf), dl);
   return mx > 0.f ? gcoef * copysignf(g, dl) : (mx == 0.f ? 0.f : mx);
 }
@@ -568,8 +569,9 @@ __global__ __launch_bounds__(kThreads) void kl_coef_kernel(KlArgs a) {
                        (nt.lam - nd.lam);
       L = kLn2D * (c + mc);
       if (lane == 0) {
-        // gradient: scale/(K T) q ln2 ((d - c) - (mu - c))
-        const double A = a.scale * static_cast<double>(a.inv_t) / K * kLn2D / sf;
+        // gradient: scale/(K T) q ln2 ((d - c) - (mu - c)); a NaN normaliser
+        // of either row (a data error) makes it NaN
+        const double A = a.scale * static_cast<double>(a.inv_t) / K * kLn2D / sf + (nt.D - nt.D) + (nd.D - nd.D);
         a.coef[static_cast<int64_t>(n) * K + kk] =
             make_float4(static_cast<float>(A), static_cast<float>(mc), 0.f, 0.f);
       }
@@ -649,7 +651,7 @@ __global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t nit
             const KlRatio rk = kl_ratio<E>(xt[j][k], xd[j][k], dr);
             if constexpr (KIND == kKlReverse) {
               const float tm = rk.wf - A.y;  // (d - c) - (mu - c)
-              gv[k] = f > 0.f ? A.x * f * tm : (f == 0.f ? 0.f : f);
+              gv[k] = f > 0.f ? A.x * f * tm : A.x * f;  // 0 where q = 0, whatever tm
             } else {
               const float e = __builtin_amdgcn_exp2f(fmaf(xt[j][k], s, -nt.M));
               gv[k] = kl_fwd_grad<E>(e, f, rk.dl, nt, nd, gcoef);

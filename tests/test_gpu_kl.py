@@ -230,3 +230,27 @@ def test_chunk_rules(N, K, V, dtype, kind):
     total = 0.5 * float(ps.double().sum()) / K
     for x in (loss, loss2):
         assert abs(float(x) - total) <= 1e-5 * abs(total) + 1e-6 * N
+
+
+@pytest.mark.parametrize("kind", ["forward", "ce", "reverse"])
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("which,V,noise", [("target", 5000, 1.0), ("draft", 5000, 1.0), ("target", 40001, 0.0),
+                                           ("draft", 40001, 0.0)])
+def test_data_errors_reach_the_gradient(which, V, noise, bad, dtype, kind):
+    """A NaN or infinite logit of either row makes the loss, the step's value
+    and its whole gradient NaN, also where the two rows are otherwise equal;
+    the other steps stay finite."""
+    N, K = 3, 2
+    d = W.tv_inputs_numpy(N, K, V, W.F32, 77)
+    if noise == 0.0:
+        d["draft"] = d["target"].copy()
+    d[which][1, 0, V // 2] = bad
+    cast = torch.bfloat16 if dtype == W.BF16 else torch.float32
+    tgt, drf = (torch.from_numpy(d[n]).cuda().to(cast) for n in ("target", "draft"))
+    loss, ps, grad = binding.kl_loss_fwd_bwd(tgt, drf, 1.0, kind, 1.0)
+    torch.cuda.synchronize()
+    assert torch.isnan(loss).all() and torch.isnan(ps[1, 0]) and torch.isnan(grad[1, 0]).all()
+    ps[1, 0] = 0.0
+    grad[1, 0] = 0.0
+    assert torch.isfinite(ps).all() and torch.isfinite(grad).all()
