@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kThreads) void tv_pair_kernel(TvArgs a, int64_t nta
           // identical rows off 1 by about 1e-6, and the loss with it)
           const float lp = fmaf(xt[j][kk], s, -nt.M) - nt.L;
           const float lq = fmaf(xd[j][kk], s, -nd.M) - nd.L;
-          const float mn = __builtin_amdgcn_exp2f(fminf(lp, lq));
+          const float mn = __builtin_amdgcn_exp2f(__builtin_elementwise_minimum(lp, lq));  // keeps NaN
           al += mn;
           const bool le = lq <= lp;
           sq += le ? mn : 0.f;
@@ -219,7 +219,8 @@ __global__ __launch_bounds__(kThreads) void tv_coef_kernel(TvArgs a) {
     x = wave_sum(x);
     y = wave_sum(y);
     z = wave_sum(z);
-    if (lane == 0) { al[wave][kk] = x; S[wave][kk] = y; Sc[wave][kk] = z; }
+    // (an overlap that is NaN, from a data error of either row, makes S and 1 - S NaN)
+    if (lane == 0) { al[wave][kk] = x; S[wave][kk] = y + (x - x); Sc[wave][kk] = z + (x - x); }
   }
   if (lane == 0) {
     double g[SPEC_MAX_K_DEV];

@@ -214,6 +214,29 @@ def test_single_read_nan_anywhere(which, V, first, count, masked, dtype, mode):
     assert torch.isnan(grad[1, 1]).all() if mode != "per_step" else torch.isfinite(grad[1, 1]).all()
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("which", ["target", "draft"])
+@pytest.mark.parametrize("dtype,V", [(W.F32, 262144), (W.BF16, 5000), (W.BF16, 600001)])
+def test_two_read_data_errors(dtype, V, which, bad):
+    """The passes that read the logits twice (forward-only calls, and gradient
+    calls whose positions span too many slices): a NaN or infinite logit of
+    either row makes the loss, the step's overlap and all of its gradient NaN."""
+    N, K = 2, 8
+    d = W.tv_inputs_numpy(N, K, V, W.F32, 9)
+    d[which][1, 0, V // 3] = bad
+    cast = torch.bfloat16 if dtype == W.BF16 else torch.float32
+    tgt, drf = (torch.from_numpy(d[n]).cuda().to(cast) for n in ("target", "draft"))
+    for mode in ("e2e", "per_step"):
+        for want_grad in (False, True):
+            loss, ov, grad = binding.tv_loss_fwd_bwd(tgt, drf, 1.0, mode, 1.0, want_grad=want_grad)
+            torch.cuda.synchronize()
+            assert torch.isnan(loss).all() and torch.isnan(ov[1, 0]), (mode, want_grad)
+            assert torch.isfinite(ov[0]).all() and torch.isfinite(ov[1, 1:]).all()
+            if want_grad:
+                assert torch.isnan(grad[1, 0]).all() and torch.isfinite(grad[0]).all(), mode
+                assert mode == "e2e" or torch.isfinite(grad[1, 1:]).all()
+
+
 def test_single_read_data_errors():
     """NaN or infinite logits make that position's loss and gradient NaN."""
     for bad in (np.nan, np.inf):
