@@ -218,7 +218,7 @@ __device__ __forceinline__ void fused_stats(const FusedCtx<E, K>& c, FusedUnit<E
 #pragma unroll
     for (int j = 0; j < kFusedNV; ++j)
 #pragma unroll
-      for (int k = 0; k < EPV; ++k) mx = fmaxf(mx, x[j][k]);
+      for (int k = 0; k < EPV; ++k) mx = max_nan(mx, x[j][k]);
     const float ref = mx * s;
     float acc = 0.f;
     if (ref != -INFINITY) {

@@ -226,7 +226,7 @@ __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typ
       weight(x, y, r);
       float mx = r[0];
 #pragma unroll
-      for (int k = 1; k < 8; ++k) mx = __builtin_elementwise_maximum(mx, r[k]);  // NaN stays
+      for (int k = 1; k < 8; ++k) mx = max_nan(mx, r[k]);
       const bool need = v0 < e1 && v0 < V && key.block(mx);
       const uint64_t m = __ballot(need);
       if (need) {
@@ -253,7 +253,7 @@ __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typ
       const Philox4x64 g = philox4x64_10(c0, static_cast<uint64_t>(static_cast<uint32_t>(v0) >> 3), c2, tag, seed, 0ull);
       float mx = key.bound(r[0], var_bound(g, 0));
 #pragma unroll
-      for (int k = 1; k < 8; ++k) mx = __builtin_elementwise_maximum(mx, key.bound(r[k], var_bound(g, k)));
+      for (int k = 1; k < 8; ++k) mx = max_nan(mx, key.bound(r[k], var_bound(g, k)));
       const bool cand = on && key.reaches(mx);
       if (__ballot(cand) != 0) {
         if (cand) {

@@ -160,7 +160,11 @@ __global__ __launch_bounds__(kThreads) void kl_stats_wave_kernel(RowsDesc d, int
 #pragma unroll
     for (int i = 0; i < S; ++i)
 #pragma unroll
-      for (int k = 0; k < EPV; ++k) mx = fmaxf(mx, x[i][k]);
+      for (int k = 0; k < EPV; ++k) mx = max_nan(mx, x[i][k]);
+    if (mx != mx) {  // (only the lane's own loop ends)
+      R = NAN;
+      break;
+    }
     if (mx > zm) {  // a new largest logit: the old one joins the other elements
       const float nr = ceilf(mx * s);
       if (zm != -INFINITY)
@@ -394,7 +398,7 @@ __device__ __forceinline__ float kl_fwd_grad(float e, float f, float dl, const K
                                              float gcoef) {
   const float pe = e * nt.invD, qf = f * nd.invD;
   // keeps NaN: a normaliser that is NaN makes every element of the row NaN
-  const float mx = __builtin_elementwise_maximum(pe, qf);
+  const float mx = max_nan(pe, qf);
   const float g = kl_absdiff<E>(mx, fminf(pe, qf), dl);
   return mx > 0.f ? gcoef * copysignf(g, dl) : (mx == 0.f ? 0.f : mx);
 }

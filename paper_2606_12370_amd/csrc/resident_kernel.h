@@ -164,8 +164,7 @@ __device__ __forceinline__ float res_uniform(float v) {
 }
 
 // (m, D) of one row's slice held in w[]: per thread a running reference over
-// CH tiles at a time, then over the workgroup's 64-lane waves.  The maximum
-// keeps NaN, so that CH tiles with nothing but NaN and -inf are not skipped.
+// CH tiles at a time, then over the workgroup's 64-lane waves.
 template <class E, int NV>
 __device__ __forceinline__ void res_stats(const typename E::vec (&w)[NV], float s, float* m, double* D) {
   constexpr int CH = 5;
@@ -179,9 +178,9 @@ __device__ __forceinline__ void res_stats(const typename E::vec (&w)[NV], float 
       float x[4];
       E::widen(w[j], x);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) mx = __builtin_elementwise_maximum(mx, x[k]);
+      for (int k = 0; k < 4; ++k) mx = max_nan(mx, x[k]);
     }
-    const float nr = __builtin_elementwise_maximum(ref, mx * s);
+    const float nr = max_nan(ref, mx * s);
     if (nr != -INFINITY) {
       const float f = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref - nr);
 #pragma unroll

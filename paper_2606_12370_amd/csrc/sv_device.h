@@ -242,6 +242,11 @@ __device__ __forceinline__ double lane(double v, int l) {
 }
 }  // namespace dpp
 
+// The larger of two floats, NaN if either is: the running maxima of the
+// statistics, which skip a step whose maximum is -inf, keep NaN, so that a
+// step with nothing but NaN and -inf is not skipped.
+__device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp::mov<dpp::kXor1>(v));
   v = fmaxf(v, dpp::mov<dpp::kXor2>(v));
@@ -550,8 +555,8 @@ __global__ __launch_bounds__(kThreads) void row_stats_wave_kernel(RowsDesc d, Ro
 #pragma unroll
       for (int i = 0; i < S; ++i)
 #pragma unroll
-        for (int k = 0; k < EPV; ++k) mx = fmaxf(mx, x[i][k]);
-      const float nr = fmaxf(ref, mx * s);
+        for (int k = 0; k < EPV; ++k) mx = max_nan(mx, x[i][k]);
+      const float nr = max_nan(ref, mx * s);
       if (nr != -INFINITY) {
         float a2 = ref == -INFINITY ? 0.f : acc * __builtin_amdgcn_exp2f(ref - nr);
 #pragma unroll

@@ -362,9 +362,9 @@ __global__ __launch_bounds__(kThreads) void diag_stats_wave_kernel(RowsDesc d, D
 #pragma unroll
     for (int i = 0; i < S; ++i)
 #pragma unroll
-      for (int k = 0; k < EPV; ++k) mx = fmaxf(mx, x[i][k]);
+      for (int k = 0; k < EPV; ++k) mx = max_nan(mx, x[i][k]);
     if (mx > zmax) { zmax = mx; zstep = st; }
-    const float nr = fmaxf(ref, mx * s);
+    const float nr = max_nan(ref, mx * s);
     if (nr != -INFINITY) {
       float acc = 0.f, acce = 0.f;
 #pragma unroll

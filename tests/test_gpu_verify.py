@@ -400,3 +400,51 @@ def test_decide_in_the_pair_pass(dtype, B, K, V):
     the launches apart, either side of the limit, for more rows than waves and
     more sub-chunks than lanes."""
     test_residual_shapes_give_identical_bits(dtype, B, K, V, "near" if B % 2 else "rollout_t")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("which", ["target", "draft"])
+@pytest.mark.parametrize("at", [0, 7, 15000, 20479])
+def test_nan_among_masked_logits(at, which, dtype):
+    """One NaN in a row masked but for a few tokens elsewhere, so that a lane's
+    whole load step holds nothing but NaN and -inf: a data error at every entry
+    point that normalises the row."""
+    B, K, V = 3, 2, 20480
+    g = torch.Generator(device="cuda")
+    g.manual_seed(at + 1)
+    tgt = torch.randn((B, K + 1, V), device="cuda", generator=g)
+    drf = torch.randn((B, K, V), device="cuda", generator=g)
+    for z in (tgt, drf):
+        z[1, 0, :4000] = z[1, 0, 4100:] = -np.inf
+    ids = torch.full((B, K), 4050, dtype=torch.int32, device="cuda")
+    (tgt if which == "target" else drf)[1, 0, at] = np.nan
+    tgt, drf = tgt.to(dtype), drf.to(dtype)
+    good = torch.tensor([0, 2], device="cuda")
+    for kw in (dict(), dict(path="single_read"), dict(path="chain", residual_shape="wave"), dict(gumbel=True),
+               dict(want_overlap=False), dict(gumbel=True, want_overlap=False)):
+        out = binding.verify(tgt, drf, ids, 1.0, 5, 1, **kw)
+        assert int(out["accept_len"][1]) == -1 and bool((out["emitted"][1] == -1).all()), kw
+        assert bool((out["accept_len"][good] >= 0).all()), kw
+        if kw.get("want_overlap", True):
+            assert bool(torch.isnan(out["overlap"][1]).all()) and bool(torch.isfinite(out["overlap"][good]).all()), kw
+    diag = binding.diagnostics(tgt, drf, 1.0)
+    assert bool(torch.isnan(diag["table"][1, 0]).all()) and int(diag["greedy_draft"][1, 0]) == -1
+    assert bool(torch.isfinite(diag["table"][good]).all()) and bool(torch.isfinite(diag["table"][1, 1]).all())
+    if which == "target":
+        out = binding.verify_target_only(tgt, ids, 1.0, 5, 1)
+        assert int(out["accept_len"][1]) == -1 and bool((out["accept_len"][good] >= 0).all())
+        rows = tgt[:, 0]
+        for T in (1.0, 0.0):
+            assert (binding.sample(rows, T, 3, 1)["tokens"] == -1).tolist() == [False, True, False]
+            assert (binding.sample_gumbel(rows, T, 3, 1)["tokens"] == -1).tolist() == [False, True, False]
+    t = tgt[:, :K].contiguous()
+    for grad in (True, False):
+        for kind in ("forward", "ce", "reverse"):
+            loss, ps, gr = binding.kl_loss_fwd_bwd(t, drf, 1.0, kind, want_grad=grad)
+            assert torch.isnan(loss).all() and torch.isnan(ps[1, 0]), (grad, kind)
+            assert bool(torch.isfinite(ps[good]).all()), (grad, kind)
+            assert gr is None or bool(torch.isfinite(gr[good]).all()), kind
+            assert gr is None or bool(torch.isnan(gr[1, 0]).all()), kind
+        loss, ov, gr = binding.tv_loss_fwd_bwd(t, drf, 1.0, "e2e", want_grad=grad)
+        assert torch.isnan(loss).all() and torch.isnan(ov[1, 0]) and bool(torch.isfinite(ov[good]).all())
+    torch.cuda.synchronize()
