@@ -108,24 +108,25 @@ struct ScanShared {
   int best;  // key_order of the workgroup's best key
 };
 
-// The keys of the draft sampler: weight z (the logit itself, so that a data
-// error is told from a finite logit whose product overflows), key a - log2 E
-// with a = z s, s > 0.
+// The keys of the draft sampler: weight a = z s, key a - log2 E.  A weight that
+// is NaN or +inf may come from a finite logit whose product overflows, so the
+// data-error test then looks at the logits (kLogits).
 struct KeyScore {
-  float s;
+  static constexpr bool kLogits = true;
   float lo;  // the best key so far, less the rounding of a key near it
   static constexpr float kNone = -INFINITY;
   __device__ __forceinline__ void set(float thr) { lo = thr - (1e-3f + 1e-6f * fabsf(thr)); }
   // whether a block whose largest weight is mx can hold such a key (NaN and +inf can)
-  __device__ __forceinline__ bool block(float mx) const { return !(mx * s + kVarMax < lo); }
-  __device__ __forceinline__ float bound(float z, float t) const { return z * s - __builtin_amdgcn_logf(t); }
+  __device__ __forceinline__ bool block(float mx) const { return !(mx + kVarMax < lo); }
+  __device__ __forceinline__ float bound(float a, float t) const { return a - __builtin_amdgcn_logf(t); }
   __device__ __forceinline__ bool reaches(float mx) const { return !(mx - 1.f < lo); }
-  __device__ __forceinline__ float key(float z, float e) const { return z * s - __builtin_amdgcn_logf(e); }
-  __device__ __forceinline__ bool counts(float z) const { return z * s > -INFINITY; }
+  static __device__ __forceinline__ float key(float a, float e) { return a - __builtin_amdgcn_logf(e); }
+  static __device__ __forceinline__ bool counts(float a) { return a > -INFINITY; }
 };
 
 // The keys of verification: weight r >= 0 (a probability or a residual), key r / E.
 struct KeyRatio {
+  static constexpr bool kLogits = false;
   float c25, c2;  // the best key so far, less its rounding, times 2^-25 and times 2
   static constexpr float kNone = 0.f;
   __device__ __forceinline__ void set(float thr) {
@@ -169,17 +170,18 @@ __device__ __forceinline__ void block_elements(const typename E::raw* row, int v
 // The best key and its first index over the elements [e0, e1) of one row
 // (e0 a multiple of kScanTile), whole workgroup.  weight(v0, x, y, r) turns a
 // block's logits (x of row rx, y of row ry where BOTH) into its weights.
-// key: the kind of keys (KeyScore with its s).  row_best (may be null): the best key that any part of the row has found so
+// row_best (may be null): the best key that any part of the row has found so
 // far, as key_order; it starts at kNone, and a bound below it at any time is
 // below the row's best key, so the results don't depend on when it is read.
 // Every thread receives the results: Key::kNone and kNoIndex where no element
-// counts.  *bad (sampler): whether a weight is NaN or +inf.
+// counts.  *bad (sampler): whether a logit is NaN or +inf.
 template <class E, class Key, bool BOTH, class Weight>
 __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typename E::raw* ry, int e0,
                                             int e1, int V, uint64_t c0, uint64_t c2, uint64_t tag,
-                                            uint64_t seed, Key key, Weight weight, int* row_best, ScanShared& sh,
+                                            uint64_t seed, Weight weight, int* row_best, ScanShared& sh,
                                             RedLds<4>& red, RedLds<1>& red1, float* best, int* index, bool* bad) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  Key key;
   float bk = Key::kNone;
   int bi = kNoIndex;
   bool isbad = false;
@@ -227,6 +229,10 @@ __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typ
       float mx = r[0];
 #pragma unroll
       for (int k = 1; k < 8; ++k) mx = max_nan(mx, r[k]);
+      if (Key::kLogits && !(mx < INFINITY)) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) isbad |= !(x[k] < INFINITY);
+      }
       const bool need = v0 < e1 && v0 < V && key.block(mx);
       const uint64_t m = __ballot(need);
       if (need) {
@@ -259,9 +265,8 @@ __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typ
         if (cand) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
-            isbad |= !(r[k] < INFINITY);
-            const float kk = key.key(r[k], exp_variate(g, k));
-            const bool better = key.counts(r[k]) & ((kk > bk) | ((kk == bk) & (v0 + k < bi)));
+            const float kk = Key::key(r[k], exp_variate(g, k));
+            const bool better = Key::counts(r[k]) & ((kk > bk) | ((kk == bk) & (v0 + k < bi)));
             bk = better ? kk : bk;
             bi = better ? v0 + k : bi;
           }
@@ -321,7 +326,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   if (residual) {
     float al = 0.f;
     gumbel_scan<E, KeyRatio, true>(
-        rt, rd, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed, KeyRatio{},
+        rt, rd, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
         [&](const float (&x)[8], const float (&y)[8], float (&r)[8]) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
@@ -342,7 +347,7 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   // mass, of which every part is without
   if (!(o.kr > 0.f)) {
     gumbel_scan<E, KeyRatio, false>(
-        rt, rt, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed, KeyRatio{},
+        rt, rt, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
         [&](const float (&x)[8], const float (&)[8], float (&r)[8]) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) r[k] = prob(x[k], s, nt.M, nt.invD);
@@ -457,10 +462,9 @@ __global__ __launch_bounds__(kThreads) void gumbel_sample_pass_kernel(GumbelSamp
   } else {
     gumbel_scan<E, KeyScore, false>(
         row, row, e0, e1, V, static_cast<uint64_t>(r), a.offset, kTagGumbelSample, a.seed,
-        KeyScore{s, 0.f},
         [&](const float (&x)[8], const float (&)[8], float (&w)[8]) {
 #pragma unroll
-          for (int k = 0; k < 8; ++k) w[k] = x[k];
+          for (int k = 0; k < 8; ++k) w[k] = x[k] * s;
         },
         a.share ? row_best_of(a, r) : nullptr, scan, red, red1, &ks, &is, &bad);
   }
