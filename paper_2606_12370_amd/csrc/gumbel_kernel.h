@@ -324,21 +324,23 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   o.kp = -1.f;
   o.ip = kNoIndex;
   if (residual) {
-    float al = 0.f;
+    double al = 0.0;  // the eight elements of a block are summed in float32, blocks in float64
     gumbel_scan<E, KeyRatio, true>(
         rt, rd, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
         [&](const float (&x)[8], const float (&y)[8], float (&r)[8]) {
+          float sum = 0.f;
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const float p = prob(x[k], s, nt.M, nt.invD);
             const float mn = fminf(p, prob(y[k], s, nd.M, nd.invD));
             r[k] = p - mn;
-            al += mn;
+            sum += mn;
           }
+          al += static_cast<double>(sum);
         },
         nullptr, scan, red, red1, &o.kr, &o.ir, &bad);
     if (a.overlap) {  // the step's overlap over this part (pair_pass_kernel leaves the step out)
-      double v[4] = {static_cast<double>(al), 0.0, 0.0, 0.0};
+      double v[4] = {al, 0.0, 0.0, 0.0};
       wg_sum<4>(v, red);
       if (threadIdx.x == 0) a.pairs[(static_cast<int64_t>(b) * K + n) * d.C + part].alpha = v[0];
     }

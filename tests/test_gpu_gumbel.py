@@ -278,3 +278,32 @@ def test_sampler_overflowing_scale(V, dtype):
     ref = sample_gumbel_ref(W.to_float64(d, dtype), T.astype(np.float64), 21, 2)
     assert ref["token"][0] == V - 1 and ref["token"][1] == 0 and (ref["token"][5:9] == -1).all()
     compare_sample_gumbel(out, ref)
+
+
+@pytest.mark.parametrize("B,V,top", [(1024, 262144, 0.99), (2048, 262144, 0.995), (1024, 1 << 21, 0.9)])
+def test_overlap_of_the_emitting_step_long_parts(B, V, top):
+    """Calls of so many rows that one workgroup scans a whole row: the
+    overlap of the rejected step, one dominant token over a flat tail whose
+    terms are about half a unit in the last place of the dominant one's share.
+    Bound: the row statistics sum 64 elements a lane in float32, 63 * 2^-24 =
+    3.8e-6 of the normaliser at worst; the overlap's float32 sums of eight add
+    at most 8 * 2^-24 = 5e-7, the probabilities' rounding 2e-7.  One float32
+    sum over the row's 1024 and more elements per thread is 1.8e-5 and more off.
+    The rows of the batch share one row's storage (stride 0)."""
+    p = np.full(V, (1.0 - top) / (V - 1))
+    p[0] = top
+    q = 0.5 * p
+    q[7] += 0.5
+    z = torch.from_numpy(np.log(np.stack([p, p, q])).astype(np.float32)).cuda()
+    tgt = z[:2].unsqueeze(0).expand(B, 2, V)
+    drf = z[2:].unsqueeze(0).expand(B, 1, V)
+    ids = torch.full((B, 1), 7, dtype=torch.int32, device="cuda")
+    out = binding.verify(tgt, drf, ids, 1.0, seed=3, offset=1, gumbel=True)
+    torch.cuda.synchronize()
+    s = torch.softmax(z.double(), -1)
+    want = float(torch.minimum(s[0], s[2]).sum())
+    ov = out["overlap"].double()[:, 0]
+    rejected = out["accept_len"] == 0
+    assert int(rejected.sum()) > B // 2
+    err = float((ov[rejected] - want).abs().max()) / want
+    assert err < 4.5e-6, err
