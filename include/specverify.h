@@ -32,15 +32,20 @@
  *    next.  Calls that share a workspace must not run concurrently (enqueue
  *    them on one stream).
  *  - Each call is a short fixed sequence of kernel launches on `stream`
- *    (spec_verify: 4, or 3 on its single-read path; spec_tv_loss_fwd_bwd:
- *    5, or 6 with a gradient; spec_verify_target_only: 2, spec_sample: 2,
+ *    (spec_verify: 4, or 3 in small calls and on its single-read path;
+ *    spec_tv_loss_fwd_bwd: 5; with a gradient 3, or 6 where its single-read
+ *    pass does not apply; spec_verify_target_only: 2, spec_sample: 2,
  *    spec_diagnostics: 4, spec_verify_gumbel: 5, or 4 without overlaps,
- *    spec_sample_gumbel: 2, spec_kl_loss_fwd_bwd: 5, or 6 with a gradient,
- *    one more for reverse KL).
- *    Only the single-read path of spec_verify has
- *    workgroups that wait for other workgroups of the same launch; it is a
- *    cooperative launch (all its workgroups resident at once) and every wait
- *    is bounded.  No other launch waits on another workgroup.
+ *    spec_sample_gumbel: 2 or 3, spec_kl_loss_fwd_bwd: 5, or 6 with a
+ *    gradient, one more for reverse KL).
+ *    Two launches have workgroups that wait for other workgroups of the same
+ *    launch, and every wait is bounded: the single-read path of spec_verify
+ *    (a cooperative launch, all its workgroups resident at once), and the
+ *    single-read pass of spec_tv_loss_fwd_bwd with a gradient (an ordinary
+ *    launch).  Where other work or a stream's CU mask keeps some of the
+ *    latter's workgroups from starting, the others stop waiting after a
+ *    quarter of a second and the next launch of the call computes what is
+ *    left, with the same bits.  No other launch waits on another workgroup.
  *  - Entry points are thread-safe; each call is independent.
  *  - Logits are bfloat16 (raw 16-bit patterns) or float32.  Arithmetic is
  *    float32 per element with float64 accumulation across vectors, threads
@@ -228,7 +233,8 @@ size_t spec_verify_noalloc_max_workspace(void);
 
 /* Bytes of workspace spec_tv_loss_fwd_bwd needs (0 on invalid sizes).  It
  * includes about one bit per logit (N*K*ceil(V/16384)*2048 bytes, about 1/32
- * of the gradient): the indicator 1[q <= p] of the forward pass, which the
+ * of the gradient): the exchange records of the single-read pass, or, where
+ * that does not apply, the indicator 1[q <= p] of the forward pass, which the
  * gradient pass reads instead of the target logits. */
 size_t spec_tv_workspace_size(int N, int K, int V, spec_dtype dtype);
 
@@ -249,7 +255,9 @@ size_t spec_tv_workspace_size(int N, int K, int V, spec_dtype dtype);
  * overlap        [N, K] float32 out (may be NULL)
  * grad_draft     [N, K, V] float32 out, contiguous; NULL = forward only
  * NaN or infinite logits propagate as NaN into that position's loss and
- * gradient (no per-position status).
+ * gradient (no per-position status).  The loss is also NaN where a
+ * workgroup of the single-read pass that has started stands still for about a
+ * second while the rest of the device runs.
  * Limits: 1 <= K <= SPEC_MAX_K, 1 <= V <= SPEC_MAX_V, 1 <= N, N*K < 2^31.
  */
 spec_status spec_tv_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, int64_t t_stride_k,

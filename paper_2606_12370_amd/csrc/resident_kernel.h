@@ -18,11 +18,18 @@
 // instead of 14 bytes per bfloat16 pair element.
 //
 // Workgroups take tickets in the order they start, and a group is K * G
-// consecutive tickets, so that every group but the last one started is
-// complete: a complete group finishes without waiting for a workgroup that
-// has not started, whatever else runs on the device.  Every wait is bounded
-// all the same; a wait that gives up raises a flag that turns the loss into
-// NaN.  The records start as all ones (kRecordEmpty) and each is one 64-bit
+// consecutive tickets and takes positions n = group, group + groups, ...  A
+// group whose workgroups have all started finishes whatever else runs on the
+// device.  That they all start is not certain: other work may hold the
+// device, or a stream's CU mask may be narrower than a group.  So a workgroup
+// whose first records stay away waits for its group to become complete, and in
+// the end marks an incomplete one as given up; no gradient is written before
+// the group is complete.  The workgroups of a marked group leave, those that
+// start later too, and tv_resident_finish_kernel computes its positions alone,
+// one workgroup a position, slice after slice with the same sums and without
+// waiting: the same bits as those of a complete group.  (A launch of its own:
+// in the main kernel that code takes registers which cost every call 2 %.)
+// The records start as all ones (kRecordEmpty) and each is one 64-bit
 // word, complete once it is not; all exchanges are relaxed agent-scope
 // atomics of whole words, so no fence is needed.  The partial sums are added
 // in slice order, so the results do not depend on timing.
@@ -38,7 +45,8 @@ constexpr int kResWaves = kResThreads / 64;
 constexpr int kResMaxGroup = 40;   // workgroups of one position (K * G)
 constexpr int kResMaxSlices = 16;  // G
 constexpr int kResWords = 6;       // exchange words per slice: (m, D, D) and (alpha, S, 1 - S)
-constexpr int kResHeadWords = 8;   // ticket and failure flag, before the records
+constexpr int kResHeadWords = 8;   // 64-bit words of counters before the records
+constexpr uint32_t kResGaveUp = 0x10000u;  // added to a group's arrivals (at most kResMaxGroup)
 
 // Tiles per row and slice held in registers: bfloat16 takes 4 registers per
 // tile and pair, float32 8, 152 of the 256 that one workgroup per CU leaves
@@ -107,9 +115,16 @@ struct ResArgs {
   int G;           // slices per row
   int tiles;       // tiles per row
   int groups;      // position groups of the launch
-  uint32_t* head;  // [0] ticket counter (starts all ones), [2] failure flag (0: a wait gave up)
+  // [0] tickets, [1] finished workgroups of the finish launch, each less one;
+  // 0 once a group gave up [2], once a complete group lost a record [3]
+  uint32_t* head;
   uint64_t* rec;   // [N][K][G][kResWords]
-  unsigned spin_limit;
+  uint32_t* state; // [groups]: arrived workgroups less one, plus kResGaveUp
+  // polls (about a microsecond each) of a workgroup: for its first position's
+  // records before it looks at its group; for the group to become complete, and
+  // the same once some group has given up; for a record of a complete group
+  unsigned first_polls, group_polls, next_group_polls, record_polls;
+  uint32_t hold;  // groups with a bit of it never count as complete (0 except in tests)
 };
 
 struct ResLds {
@@ -118,6 +133,7 @@ struct ResLds {
   float c[8];   // rt, rd, tau, -, A1, A0
   double cc[2]; // cT, cD
   uint32_t ticket;
+  uint32_t arrival;  // the group's state before this workgroup arrived
   int fail;
 };
 
@@ -128,26 +144,6 @@ __device__ __forceinline__ uint64_t res_word(double v) {
 __device__ __forceinline__ uint64_t res_word(float a, float b) {
   const uint64_t w = (static_cast<uint64_t>(__float_as_uint(b)) << 32) | __float_as_uint(a);
   return w == kRecordEmpty ? w - 1 : w;
-}
-
-// One wave: `W` consecutive words of the lanes with `on`, once they are
-// complete, or kRecordEmpty in the place of a word where the wait gave up
-// (*ok false).
-template <int W>
-__device__ __forceinline__ void res_wait(const uint64_t* p, bool on, unsigned limit, uint64_t (&v)[W], bool* ok) {
-#pragma unroll
-  for (int i = 0; i < W; ++i) v[i] = on ? kRecordEmpty : 0;
-  for (unsigned s = 0; s < limit; ++s) {
-    bool wait = false;
-#pragma unroll
-    for (int i = 0; i < W; ++i)
-      if (on) v[i] = ld_agent(p + i);
-#pragma unroll
-    for (int i = 0; i < W; ++i) wait = wait || v[i] == kRecordEmpty;
-    if (__ballot(wait) == 0) return;
-    __builtin_amdgcn_s_sleep(1);
-  }
-  *ok = false;
 }
 
 // One wave: the statistics (m, D) of up to 64 parts, one per lane (-inf, 0
@@ -203,6 +199,305 @@ __device__ __forceinline__ void res_stats(const typename E::vec (&w)[NV], float 
   *D = wave_sum(d);
 }
 
+// One thread of a workgroup of group grp: true once all `need` workgroups of the
+// group have started, false once the group has given up, which this one
+// marks after its polls.  (A round per arrival may follow: the mark is set
+// only on an incomplete group.)
+__device__ __forceinline__ bool res_formed(const ResArgs& r, int grp, uint32_t need) {
+  uint32_t* st = r.state + grp;
+  for (unsigned s = 0;; ++s) {
+    const uint32_t v = __hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t flag = __hip_atomic_load(r.head + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v + 1u == need) return true;
+    if (v + 1u >= kResGaveUp) return false;
+    if (s >= (flag == 0u ? r.next_group_polls : r.group_polls)) {
+      uint32_t seen = v;
+      if (__hip_atomic_compare_exchange_strong(st, &seen, v + kResGaveUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT)) {
+        __hip_atomic_store(r.head + 2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+      }
+      continue;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+// Wave 0: three consecutive words of the lanes with `on`, once they are
+// complete and (FIRST) the counter *st, less one, is at `need`; false after
+// `polls` looks.
+template <bool FIRST>
+__device__ __forceinline__ bool res_poll(const uint64_t* p, bool on, unsigned polls, const uint32_t* st,
+                                         uint32_t need, uint64_t (&v)[3]) {
+  for (unsigned s = 0; s < polls; ++s) {
+    bool wait = FIRST && threadIdx.x == 0 &&
+                __hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != need;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      v[i] = on ? ld_agent(p + i) : 0;
+      wait = wait || v[i] == kRecordEmpty;
+    }
+    if (__ballot(wait) == 0) return true;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return false;
+}
+
+// The wait of an exchange; false: the group has given up, or the records of a
+// complete group stay away (its workgroups all run, so that takes a device
+// that stops one of them for a second; head[3] then makes the loss NaN).  At
+// the group's first position (`first`) the group itself must be complete too: a
+// complete group is never marked as given up, so no group that is marked has
+// written any of its gradient.
+template <bool ALONE>
+__device__ __forceinline__ bool res_wait(const ResArgs& r, int grp, int PG, bool first, const uint64_t* p, bool on,
+                                         uint64_t (&v)[3]) {
+  if (!ALONE && first) {
+    const uint32_t need = static_cast<uint32_t>(PG) + (static_cast<uint32_t>(grp) & r.hold);
+    if (res_poll<true>(p, on, r.first_polls, r.state + grp, need, v)) return true;
+    int formed = 0;
+    if (threadIdx.x == 0) formed = res_formed(r, grp, need) ? 1 : 0;
+    if (__builtin_amdgcn_readfirstlane(formed) == 0) return false;
+  }
+  const bool ok = res_poll<false>(p, on, ALONE ? 1u << 20 : r.record_polls, nullptr, 0u, v);
+  if (!ALONE && !ok && threadIdx.x == 0)
+    __hip_atomic_store(r.head + 3, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return ok;
+}
+
+// What a workgroup holds of a pair: slice w of step k.  Slot j holds tile
+// tb + j, for the slots from j0: the slice's last tile, the only one that can
+// reach past the row, is in the last slot.  There the last `over` elements of
+// a vector lie past the row: the row's last whole vector is read in its place,
+// shifted down and filled with -inf.
+struct ResSlice {
+  int k, w, mem, j0, tb, vlast, over;
+};
+template <class E, int NV>
+__device__ __forceinline__ ResSlice res_slice_of(const ResArgs& r, int mem, int V) {
+  constexpr int TILE = kResThreads * E::EPV;
+  ResSlice c;
+  c.mem = mem;
+  c.k = mem / r.G;
+  c.w = mem - c.k * r.G;
+  const int t0 = static_cast<int>(static_cast<int64_t>(c.w) * r.tiles / r.G);
+  const int nt = static_cast<int>(static_cast<int64_t>(c.w + 1) * r.tiles / r.G) - t0;
+  c.j0 = NV - nt;
+  c.tb = t0 - c.j0;
+  c.vlast = (c.tb + NV - 1) * TILE + static_cast<int>(threadIdx.x) * E::EPV;
+  c.over = min(max(c.vlast + E::EPV - V, 0), E::EPV);
+  return c;
+}
+template <class E, int NV>
+__device__ __forceinline__ typename E::vec res_tile_load(const ResSlice& c, const typename E::raw* row, int j, int V) {
+  constexpr int TILE = kResThreads * E::EPV;
+  if (j == NV - 1) return load_vec<E>(row + (c.over > 0 ? V - E::EPV : c.vlast));
+  const char* base = reinterpret_cast<const char*>(row + static_cast<int64_t>(c.tb + j) * TILE);
+  return load_any(reinterpret_cast<const typename E::any*>(base + threadIdx.x * static_cast<uint32_t>(sizeof(typename E::vec))));
+}
+template <class E>
+__device__ __forceinline__ const typename E::raw* res_row_t(const RowsDesc& d, int n, int k) {
+  return static_cast<const typename E::raw*>(d.tgt) + static_cast<int64_t>(n) * d.tsb + static_cast<int64_t>(k) * d.tsk;
+}
+template <class E>
+__device__ __forceinline__ const typename E::raw* res_row_d(const RowsDesc& d, int n, int k) {
+  return static_cast<const typename E::raw*>(d.drf) + static_cast<int64_t>(n) * d.dsb + static_cast<int64_t>(k) * d.dsk;
+}
+
+// A workgroup's part of position n, its slice loaded in xt / xd; behind the
+// gradient the loads of position nn (if below N).  With ALONE one workgroup
+// takes all slices of the position in turn, and the call ends after stage
+// `stages`: 1 the statistics published, 2 the sums published, 3 the gradient.
+// False: the group has given up (or lost a record).
+template <class E, int NV, bool ALONE>
+__device__ __forceinline__ bool res_position(const TvArgs& a, const ResArgs& r, const ResSlice& c, int n, int nn,
+                                             int grp, int stages,
+                                             typename E::vec (&xt)[NV], typename E::vec (&xd)[NV], ResLds& sh) {
+  constexpr int EPV = E::EPV;
+  static_assert(EPV == 4, "four elements per vector");
+  constexpr int TILE = kResThreads * EPV;
+  const RowsDesc& d = a.rows;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int K = a.K, V = d.V, G = r.G, PG = K * G;
+  const float s = scale_of(d.temp_scalar);
+  const bool first = !ALONE && n == grp;  // the group may not be complete yet
+  res_shift(xt[NV - 1], c.over);
+  res_shift(xd[NV - 1], c.over);
+  float mt, md;
+  double Dt, Dd;
+  res_stats<E, NV>(xt, s, &mt, &Dt);
+  res_stats<E, NV>(xd, s, &md, &Dd);
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    res_opaque(xt[j]);
+    res_opaque(xd[j]);
+  }
+  if (lane == 0) {
+    sh.red[wave][0] = static_cast<double>(mt);
+    sh.red[wave][1] = Dt;
+    sh.red[wave][2] = static_cast<double>(md);
+    sh.red[wave][3] = Dd;
+  }
+  __syncthreads();
+  uint64_t* rec = r.rec + (static_cast<int64_t>(n) * K + c.k) * G * kResWords;
+  bool ok = true;  // (wave 0) the group has not given up
+  if (wave == 0) {
+    // the workgroup's waves, then the group's slices, one per lane
+    float m2[2] = {-INFINITY, -INFINITY};
+    double D2[2] = {0.0, 0.0};
+    if (lane < kResWaves) {
+      m2[0] = static_cast<float>(sh.red[lane][0]);
+      D2[0] = sh.red[lane][1];
+      m2[1] = static_cast<float>(sh.red[lane][2]);
+      D2[1] = sh.red[lane][3];
+    }
+    res_combine(m2[0], D2[0]);
+    res_combine(m2[1], D2[1]);
+    if (ALONE && stages == 1 && G == 1) return true;
+    if (G > 1) {
+      if (lane < 3)
+        st_agent(rec + c.w * kResWords + lane,
+                 lane == 0 ? res_word(m2[0], m2[1]) : (lane == 1 ? res_word(D2[0]) : res_word(D2[1])));
+      if (ALONE && stages == 1) return true;
+    }
+    ok = !first || sh.arrival + 1u < kResGaveUp;  // (given up before this workgroup started)
+    if (G > 1 && ok) {
+      uint64_t v[3];
+      ok = res_wait<ALONE>(r, grp, PG, first, rec + lane * kResWords, lane < G, v);
+      const bool on = lane < G;
+      m2[0] = on ? __uint_as_float(static_cast<uint32_t>(v[0])) : -INFINITY;
+      m2[1] = on ? __uint_as_float(static_cast<uint32_t>(v[0] >> 32)) : -INFINITY;
+      D2[0] = on ? __longlong_as_double(static_cast<long long>(v[1])) : 0.0;
+      D2[1] = on ? __longlong_as_double(static_cast<long long>(v[2])) : 0.0;
+      res_combine(m2[0], D2[0]);
+      res_combine(m2[1], D2[1]);
+    }
+    // p = 2^(z_t s - rt) cT and q = 2^(z_d s - rd) cD, r the row's
+    // M + log2 D rounded to float32 and c = 2^(r - (M + log2 D)) its
+    // rounding; q <= p exactly where z_d - z_t <= tau.  Lane 0 forms the
+    // target's, lane 1 the draft's.
+    const double lz = static_cast<double>(lane == 0 ? m2[0] : m2[1]) + log2(lane == 0 ? D2[0] : D2[1]);
+    const float rz = static_cast<float>(lz);
+    if (lane < 2) {
+      sh.c[lane] = rz;
+      sh.cc[lane] = exp2(static_cast<double>(rz) - lz);
+    }
+    const double td = (dpp::lane(lz, 1) - dpp::lane(lz, 0)) / static_cast<double>(s);
+    float tau = static_cast<float>(td);
+    if (static_cast<double>(tau) > td) tau = nextafterf(tau, -INFINITY);
+    if (lane == 0) {
+      sh.c[2] = tau;
+      if (!ALONE && !ok) sh.fail = 1;
+    }
+  } else if (ALONE && stages == 1) {
+    return true;
+  }
+  __syncthreads();
+  if (first && sh.fail) return false;  // (uniform; at a later position below)
+  float ap = 0.f, aq = 0.f, sc = 0.f;
+  {
+    const float rt = res_uniform(sh.c[0]), rd = res_uniform(sh.c[1]), tau = res_uniform(sh.c[2]);
+    const int jp = res_opaque_s(c.j0);
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+      if (j >= jp) {
+        float zt[4], zd[4], o[4];
+        E::widen(xt[j], zt);
+        E::widen(xd[j], zd);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float ep = __builtin_amdgcn_exp2f(fmaf(zt[i], s, -rt));
+          const float eq = __builtin_amdgcn_exp2f(fmaf(zd[i], s, -rd));
+          const bool le = zd[i] - zt[i] <= tau;
+          ap += le ? 0.f : ep;
+          aq += le ? eq : 0.f;
+          sc += le ? 0.f : eq;
+          o[i] = le ? eq : -eq;
+        }
+        res_put(xt[j], xd[j], o);
+      }
+  }
+  const double sp = wave_sum(static_cast<double>(ap)), sq = wave_sum(static_cast<double>(aq)),
+               sx = wave_sum(static_cast<double>(sc));
+  if (lane == 0) {
+    sh.red[wave][0] = sp;
+    sh.red[wave][1] = sq;
+    sh.red[wave][2] = sx;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const bool on = lane < kResWaves;
+    const double p = wave_sum(on ? sh.red[lane][0] : 0.0), q = wave_sum(on ? sh.red[lane][1] : 0.0),
+                 x = wave_sum(on ? sh.red[lane][2] : 0.0);
+    const double cT = sh.cc[0], cD = sh.cc[1];
+    // (a target normaliser that is NaN makes S and 1 - S NaN as well)
+    const double part[3] = {cT * p + cD * q, cD * q + (cT - cT), cD * x + (cT - cT)};
+    if (lane < 3 && ok)
+      st_agent(rec + c.w * kResWords + 3 + lane, res_word(lane == 0 ? part[0] : (lane == 1 ? part[1] : part[2])));
+    if (ALONE && stages == 2) return true;
+    const uint64_t* all = r.rec + static_cast<int64_t>(n) * PG * kResWords;
+    uint64_t v[3];
+    if (ok) ok = res_wait<ALONE>(r, grp, PG, first, all + lane * kResWords + 3, lane < PG, v);
+    if (lane < PG)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) sh.x[lane * 3 + i] = __longlong_as_double(static_cast<long long>(v[i]));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // lane i < K: step i's alpha, S and 1 - S, slices in order
+    double al = 0.0, S = 0.0, Sc = 0.0;
+    if (lane < K)
+      for (int i = 0; i < G; ++i) {
+        al += sh.x[(lane * G + i) * 3];
+        S += sh.x[(lane * G + i) * 3 + 1];
+        Sc += sh.x[(lane * G + i) * 3 + 2];
+      }
+    double gk, L;
+    chain_factor_of(K, a.mode, c.k, [&](int i) -> double { return dpp::lane(al, i); }, &gk, &L);
+    gk = a.scale * gk * static_cast<double>(a.inv_t);
+    const double A1 = gk * dpp::lane(Sc, c.k) * sh.cc[1], A0 = -gk * dpp::lane(S, c.k) * sh.cc[1];
+    if (lane == 0) {
+      sh.c[4] = static_cast<float>(A1);
+      sh.c[5] = static_cast<float>(A0);
+      if (!ALONE && !ok) sh.fail = 1;
+      if (c.mem == 0 && ok) a.loss_pos[n] = a.scale * L;
+    }
+    if (c.mem == 0 && ok && a.overlap && lane < K) a.overlap[static_cast<int64_t>(n) * K + lane] = static_cast<float>(al);
+  } else if (ALONE && stages == 2) {
+    return true;
+  }
+  __syncthreads();
+  if (!ALONE && sh.fail) return false;  // (uniform)
+  // the gradient, and the next position's loads of each tile behind it
+  const bool more = !ALONE && nn < a.N;
+  const typename E::raw *rt = res_row_t<E>(d, more ? nn : n, c.k), *rd = res_row_d<E>(d, more ? nn : n, c.k);
+  const float A1 = res_uniform(sh.c[4]), nA0 = -res_uniform(sh.c[5]);
+  float* gr = a.grad + (static_cast<int64_t>(n) * K + c.k) * V;
+  const int jw = res_opaque_s(c.j0);
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+    if (j >= jw) {
+      float o[4];
+      res_get(xt[j], xd[j], o);
+      f32x4 g;
+      g.x = o[0] * (o[0] < 0.f ? nA0 : A1);
+      g.y = o[1] * (o[1] < 0.f ? nA0 : A1);
+      g.z = o[2] * (o[2] < 0.f ? nA0 : A1);
+      g.w = o[3] * (o[3] < 0.f ? nA0 : A1);
+      char* base = reinterpret_cast<char*>(gr + static_cast<int64_t>(c.tb + j) * TILE);
+      if (j < NV - 1 || c.over == 0) {
+        __builtin_nontemporal_store(g, reinterpret_cast<f32x4_any*>(base + static_cast<uint32_t>(tid) * 16u));
+      } else {
+        if (c.over < 4) gr[c.vlast] = g.x;
+        if (c.over < 3) gr[c.vlast + 1] = g.y;
+        if (c.over < 2) gr[c.vlast + 2] = g.z;
+      }
+      if (more) {
+        xt[j] = res_tile_load<E, NV>(c, rt, j, V);
+        xd[j] = res_tile_load<E, NV>(c, rd, j, V);
+      }
+    }
+  return true;
+}
+
 // Moves 8 bytes per bfloat16 pair element (both logits read, the gradient
 // written) against the 14 of the passes in tv_kernel.h.  Bound by the parts
 // of a position that do not overlap on a CU: of 35 us per position (V =
@@ -212,235 +507,91 @@ __device__ __forceinline__ void res_stats(const typename E::vec (&w)[NV], float 
 // -> 3.49 ms a call in bfloat16; N = 1024 in float32 1.92 -> 1.30 ms.
 template <class E, int NV>
 __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, ResArgs r) {
-  using vec = typename E::vec;
-  constexpr int EPV = E::EPV;
-  static_assert(EPV == 4, "four elements per vector");
-  constexpr int TILE = kResThreads * EPV;
   __shared__ ResLds sh;
   const RowsDesc& d = a.rows;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int K = a.K, V = d.V, G = r.G, PG = K * G;
-  if (tid == 0) {
+  const int PG = a.K * r.G;
+  if (threadIdx.x == 0) {
     sh.ticket = atomicAdd(r.head, 1u) + 1u;
     sh.fail = 0;
   }
   __syncthreads();
   const int tk = __builtin_amdgcn_readfirstlane(static_cast<int>(sh.ticket));
-  const int grp = tk / PG, mem = tk - grp * PG;
-  const int k = mem / G, w = mem - k * G;
-  const int t0 = static_cast<int>(static_cast<int64_t>(w) * r.tiles / G);
-  const int nt = static_cast<int>(static_cast<int64_t>(w + 1) * r.tiles / G) - t0;
-  // slot j holds tile tb + j, for the slots from NV - nt: the slice's last
-  // tile, the only one that can reach past the row, is in the last slot
-  const int j0 = NV - nt, tb = t0 - j0;
-  const float s = scale_of(d.temp_scalar);
-  vec xt[NV], xd[NV];
+  const int grp = tk / PG;
+  const ResSlice c = res_slice_of<E, NV>(r, tk - grp * PG, d.V);
+  const uint32_t arrival = threadIdx.x == 0 ? atomicAdd(r.state + grp, 1u) : 0u;
+  typename E::vec xt[NV], xd[NV];
 #pragma unroll
   for (int j = 0; j < NV; ++j) xt[j] = xd[j] = res_neg_inf(static_cast<const E*>(nullptr));
-
-  // byte offset of this thread's vector inside a tile; in the last slot the
-  // last `over` elements of a vector lie past the row: the row's last whole
-  // vector is read in its place, shifted down and filled with -inf
-  const uint32_t voff = static_cast<uint32_t>(tid) * sizeof(vec);
-  const int vlast = (tb + NV - 1) * TILE + tid * EPV;
-  const int over = min(max(vlast + EPV - V, 0), EPV);
-  auto tile_load = [&](const typename E::raw* row, int j) -> vec {
-    if (j == NV - 1) return load_vec<E>(row + (over > 0 ? V - EPV : vlast));
-    const char* base = reinterpret_cast<const char*>(row + static_cast<int64_t>(tb + j) * TILE);
-    return load_any(reinterpret_cast<const typename E::any*>(base + voff));
-  };
-  auto row_t = [&](int n) {
-    return static_cast<const typename E::raw*>(d.tgt) + static_cast<int64_t>(n) * d.tsb + static_cast<int64_t>(k) * d.tsk;
-  };
-  auto row_d = [&](int n) {
-    return static_cast<const typename E::raw*>(d.drf) + static_cast<int64_t>(n) * d.dsb + static_cast<int64_t>(k) * d.dsk;
-  };
   if (grp < a.N) {
-    const typename E::raw *rt = row_t(grp), *rd = row_d(grp);
+    const typename E::raw *rt = res_row_t<E>(d, grp, c.k), *rd = res_row_d<E>(d, grp, c.k);
 #pragma unroll
     for (int j = 0; j < NV; ++j)
-      if (j >= j0) {
-        xt[j] = tile_load(rt, j);
-        xd[j] = tile_load(rd, j);
+      if (j >= c.j0) {
+        xt[j] = res_tile_load<E, NV>(c, rt, j, d.V);
+        xd[j] = res_tile_load<E, NV>(c, rd, j, d.V);
       }
   }
-  for (int n = grp; n < a.N; n += r.groups) {
-    res_shift(xt[NV - 1], over);
-    res_shift(xd[NV - 1], over);
-    float mt, md;
-    double Dt, Dd;
-    res_stats<E, NV>(xt, s, &mt, &Dt);
-    res_stats<E, NV>(xd, s, &md, &Dd);
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      res_opaque(xt[j]);
-      res_opaque(xd[j]);
-    }
-    if (lane == 0) {
-      sh.red[wave][0] = static_cast<double>(mt);
-      sh.red[wave][1] = Dt;
-      sh.red[wave][2] = static_cast<double>(md);
-      sh.red[wave][3] = Dd;
-    }
-    __syncthreads();
-    uint64_t* rec = r.rec + (static_cast<int64_t>(n) * K + k) * G * kResWords;
-    if (wave == 0) {
-      // the workgroup's waves, then the group's slices, one per lane
-      float m2[2] = {-INFINITY, -INFINITY};
-      double D2[2] = {0.0, 0.0};
-      if (lane < kResWaves) {
-        m2[0] = static_cast<float>(sh.red[lane][0]);
-        D2[0] = sh.red[lane][1];
-        m2[1] = static_cast<float>(sh.red[lane][2]);
-        D2[1] = sh.red[lane][3];
-      }
-      res_combine(m2[0], D2[0]);
-      res_combine(m2[1], D2[1]);
-      bool ok = true;
-      if (G > 1) {
-        if (lane < 3)
-          st_agent(rec + w * kResWords + lane,
-                   lane == 0 ? res_word(m2[0], m2[1]) : (lane == 1 ? res_word(D2[0]) : res_word(D2[1])));
-        uint64_t v[3];
-        res_wait<3>(rec + lane * kResWords, lane < G, r.spin_limit, v, &ok);
-        const bool on = lane < G;
-        m2[0] = on ? __uint_as_float(static_cast<uint32_t>(v[0])) : -INFINITY;
-        m2[1] = on ? __uint_as_float(static_cast<uint32_t>(v[0] >> 32)) : -INFINITY;
-        D2[0] = on ? __longlong_as_double(static_cast<long long>(v[1])) : 0.0;
-        D2[1] = on ? __longlong_as_double(static_cast<long long>(v[2])) : 0.0;
-        res_combine(m2[0], D2[0]);
-        res_combine(m2[1], D2[1]);
-      }
-      // p = 2^(z_t s - rt) cT and q = 2^(z_d s - rd) cD, r the row's
-      // M + log2 D rounded to float32 and c = 2^(r - (M + log2 D)) its
-      // rounding; q <= p exactly where z_d - z_t <= tau.  Lane 0 forms the
-      // target's, lane 1 the draft's.
-      const double lz = static_cast<double>(lane == 0 ? m2[0] : m2[1]) + log2(lane == 0 ? D2[0] : D2[1]);
-      const float rz = static_cast<float>(lz);
-      if (lane < 2) {
-        sh.c[lane] = rz;
-        sh.cc[lane] = exp2(static_cast<double>(rz) - lz);
-      }
-      const double td = (dpp::lane(lz, 1) - dpp::lane(lz, 0)) / static_cast<double>(s);
-      float tau = static_cast<float>(td);
-      if (static_cast<double>(tau) > td) tau = nextafterf(tau, -INFINITY);
-      if (lane == 0) {
-        sh.c[2] = tau;
-        if (!ok) sh.fail = 1;
-      }
-    }
-    __syncthreads();
-    float ap = 0.f, aq = 0.f, sc = 0.f;
-    {
-      const float rt = res_uniform(sh.c[0]), rd = res_uniform(sh.c[1]), tau = res_uniform(sh.c[2]);
-      const int jp = res_opaque_s(j0);
-#pragma unroll
-      for (int j = 0; j < NV; ++j)
-        if (j >= jp) {
-          float zt[4], zd[4], o[4];
-          E::widen(xt[j], zt);
-          E::widen(xd[j], zd);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float ep = __builtin_amdgcn_exp2f(fmaf(zt[i], s, -rt));
-            const float eq = __builtin_amdgcn_exp2f(fmaf(zd[i], s, -rd));
-            const bool le = zd[i] - zt[i] <= tau;
-            ap += le ? 0.f : ep;
-            aq += le ? eq : 0.f;
-            sc += le ? 0.f : eq;
-            o[i] = le ? eq : -eq;
-          }
-          res_put(xt[j], xd[j], o);
-        }
-    }
-    const double sp = wave_sum(static_cast<double>(ap)), sq = wave_sum(static_cast<double>(aq)),
-                 sx = wave_sum(static_cast<double>(sc));
-    if (lane == 0) {
-      sh.red[wave][0] = sp;
-      sh.red[wave][1] = sq;
-      sh.red[wave][2] = sx;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const bool on = lane < kResWaves;
-      const double p = wave_sum(on ? sh.red[lane][0] : 0.0), q = wave_sum(on ? sh.red[lane][1] : 0.0),
-                   x = wave_sum(on ? sh.red[lane][2] : 0.0);
-      const double cT = sh.cc[0], cD = sh.cc[1];
-      // (a target normaliser that is NaN makes S and 1 - S NaN as well)
-      const double part[3] = {cT * p + cD * q, cD * q + (cT - cT), cD * x + (cT - cT)};
-      if (lane < 3) st_agent(rec + w * kResWords + 3 + lane, res_word(lane == 0 ? part[0] : (lane == 1 ? part[1] : part[2])));
-      bool ok = true;
-      const uint64_t* all = r.rec + static_cast<int64_t>(n) * PG * kResWords;
-      uint64_t v[3];
-      res_wait<3>(all + lane * kResWords + 3, lane < PG, r.spin_limit, v, &ok);
-      if (lane < PG)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) sh.x[lane * 3 + i] = __longlong_as_double(static_cast<long long>(v[i]));
-      if (lane == 0 && !ok) sh.fail = 1;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      // lane i < K: step i's alpha, S and 1 - S, slices in order
-      double al = 0.0, S = 0.0, Sc = 0.0;
-      if (lane < K)
-        for (int i = 0; i < G; ++i) {
-          al += sh.x[(lane * G + i) * 3];
-          S += sh.x[(lane * G + i) * 3 + 1];
-          Sc += sh.x[(lane * G + i) * 3 + 2];
-        }
-      double gk, L;
-      chain_factor_of(K, a.mode, k, [&](int i) -> double { return dpp::lane(al, i); }, &gk, &L);
-      gk = a.scale * gk * static_cast<double>(a.inv_t);
-      const double A1 = gk * dpp::lane(Sc, k) * sh.cc[1], A0 = -gk * dpp::lane(S, k) * sh.cc[1];
-      if (lane == 0) {
-        sh.c[4] = static_cast<float>(A1);
-        sh.c[5] = static_cast<float>(A0);
-        if (mem == 0) a.loss_pos[n] = a.scale * L;
-        if (sh.fail) st_agent(reinterpret_cast<uint64_t*>(r.head + 2), 0ull);
-      }
-      if (mem == 0 && a.overlap && lane < K) a.overlap[static_cast<int64_t>(n) * K + lane] = static_cast<float>(al);
-    }
-    __syncthreads();
-    if (sh.fail) return;  // (uniform) a wait gave up: the loss becomes NaN
-    // the gradient, and the next position's loads of each tile behind it
-    const int nn = n + r.groups;
-    const bool more = nn < a.N;
-    const typename E::raw *rt = row_t(more ? nn : n), *rd = row_d(more ? nn : n);
-    const float A1 = res_uniform(sh.c[4]), nA0 = -res_uniform(sh.c[5]);
-    float* gr = a.grad + (static_cast<int64_t>(n) * K + k) * V;
-    const int jw = res_opaque_s(j0);
-#pragma unroll
-    for (int j = 0; j < NV; ++j)
-      if (j >= jw) {
-        float o[4];
-        res_get(xt[j], xd[j], o);
-        f32x4 g;
-        g.x = o[0] * (o[0] < 0.f ? nA0 : A1);
-        g.y = o[1] * (o[1] < 0.f ? nA0 : A1);
-        g.z = o[2] * (o[2] < 0.f ? nA0 : A1);
-        g.w = o[3] * (o[3] < 0.f ? nA0 : A1);
-        char* base = reinterpret_cast<char*>(gr + static_cast<int64_t>(tb + j) * TILE);
-        if (j < NV - 1 || over == 0) {
-          __builtin_nontemporal_store(g, reinterpret_cast<f32x4_any*>(base + static_cast<uint32_t>(tid) * 16u));
-        } else {
-          if (over < 4) gr[vlast] = g.x;
-          if (over < 3) gr[vlast + 1] = g.y;
-          if (over < 2) gr[vlast + 2] = g.z;
-        }
-        if (more) {
-          xt[j] = tile_load(rt, j);
-          xd[j] = tile_load(rd, j);
-        }
-      }
-  }
+  if (threadIdx.x == 0) sh.arrival = arrival;  // (behind the loads: the atomic is on its way)
+  for (int n = grp; n < a.N; n += r.groups)
+    if (!res_position<E, NV, false>(a, r, c, n, n + r.groups, grp, 3, xt, xd, sh)) return;
 }
 
-// The total loss (tv_loss_kernel), NaN where a wait of the resident pass gave up.
-__global__ __launch_bounds__(kThreads) void tv_resident_loss_kernel(TvArgs a, const uint32_t* __restrict__ head) {
-  __shared__ RedLds<1> red;
+// The positions of groups that gave up (none as a rule: one load tells), then
+// the total loss, the position losses added in tv_loss_kernel's order, NaN
+// where a complete group lost a record.
+template <class E, int NV>
+__global__ __launch_bounds__(kResThreads, 2) void tv_resident_finish_kernel(TvArgs a, ResArgs r) {
+  __shared__ ResLds sh;
+  const RowsDesc& d = a.rows;
+  const int tid = threadIdx.x, PG = a.K * r.G;
+  auto losses = [&]() -> double {
+    double acc = 0.0;
+    if (tid < kThreads)
+      for (int p = tid; p < a.N; p += kThreads) acc += a.loss_pos[p];
+    return acc;
+  };
+  const uint32_t flag = r.head[2], lost = r.head[3];
   double acc = 0.0;
-  for (int p = threadIdx.x; p < a.N; p += kThreads) acc += a.loss_pos[p];
-  double v[1] = {acc};
-  wg_sum<1>(v, red);
-  if (threadIdx.x == 0) *a.loss = head[2] == 0u ? NAN : static_cast<float>(v[0]);
+  if (blockIdx.x == 0) acc = losses();  // (with the flags still on their way)
+  if (flag != 0u) {
+    if (blockIdx.x != 0) return;
+  } else {
+    for (int n = blockIdx.x; n < a.N; n += static_cast<int>(gridDim.x)) {
+      if (r.state[n % r.groups] + 1u < kResGaveUp) continue;
+      for (int stages = 1; stages <= 3; ++stages)
+        for (int mem = 0; mem < PG; ++mem) {
+          const ResSlice c = res_slice_of<E, NV>(r, mem, d.V);
+          const typename E::raw *rt = res_row_t<E>(d, n, c.k), *rd = res_row_d<E>(d, n, c.k);
+          typename E::vec xt[NV], xd[NV];
+#pragma unroll
+          for (int j = 0; j < NV; ++j) {
+            xt[j] = xd[j] = res_neg_inf(static_cast<const E*>(nullptr));
+            if (j >= c.j0) {
+              xt[j] = res_tile_load<E, NV>(c, rt, j, d.V);
+              xd[j] = res_tile_load<E, NV>(c, rd, j, d.V);
+            }
+          }
+          res_position<E, NV, true>(a, r, c, n, a.N, 0, stages, xt, xd, sh);
+          __syncthreads();
+        }
+    }
+    // the last workgroup to finish adds the losses
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) sh.ticket = atomicAdd(r.head + 1, 1u) + 1u;
+    __syncthreads();
+    if (sh.ticket != gridDim.x - 1u) return;
+    __threadfence();
+    acc = losses();
+  }
+  acc = wave_sum(acc);
+  if ((tid & 63) == 0) sh.red[tid >> 6][0] = acc;
+  __syncthreads();
+  if (tid == 0) {
+    double v = sh.red[0][0];
+    for (int w = 1; w < kWaves; ++w) v += sh.red[w][0];
+    *a.loss = lost == 0u ? NAN : static_cast<float>(v);
+  }
 }
 
 }  // namespace sv

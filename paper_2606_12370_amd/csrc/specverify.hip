@@ -491,6 +491,9 @@ const ResFacts* res_facts() {
   return &f;
 }
 
+// Workgroups of the finish launch, which all but one leave at once as a rule.
+constexpr int kResFinishWgs = 256;
+
 struct ResPlan {
   int G = 0, groups = 0, tiles = 0;
 };
@@ -519,11 +522,21 @@ ResPlan res_plan(int N, int K, int V, int nv, int epv, int slots) {
   return p;
 }
 
-// The single-read pass for calls with a gradient.  Without a gradient its exchanges are not hidden behind any
-// writes: N = 4096, K = 3, V = 151936 bfloat16 2.52 ms against 2.43 for the
-// passes that read twice.
+// Polls of the waits (about a microsecond each): 64 before a workgroup looks at
+// its group at all; a quarter of a second for the group to become complete
+// (as long as a call that fills the card's memory holds the device); once a
+// group has given up a quarter of a millisecond, so that on a stream too
+// narrow for any group the others stop waiting soon.
+struct ResWaits {
+  unsigned first = 64, group = 1u << 18, next_group = 256, record = 1u << 20;
+  unsigned hold = 0;  // see ResArgs
+};
+
+// The single-read pass for calls with a gradient.  Without a gradient its
+// exchanges are not hidden behind any writes: N = 4096, K = 3, V = 151936
+// bfloat16 2.52 ms against 2.43 for the passes that read twice.
 template <class E>
-bool launch_tv_resident(const sv::TvArgs& a, void* ws, hipStream_t s, spec_status* st) {
+bool launch_tv_resident(const sv::TvArgs& a, void* ws, hipStream_t s, const ResWaits& waits, spec_status* st) {
   const spec_dtype dt = std::is_same<E, BF16>::value ? SPEC_BF16 : SPEC_F32;
   using G = typename GradElem<E>::type;
   constexpr int NV = sv::ResCap<G>::NV;
@@ -539,22 +552,30 @@ bool launch_tv_resident(const sv::TvArgs& a, void* ws, hipStream_t s, spec_statu
   r.groups = p.groups;
   r.head = static_cast<uint32_t*>(ws);
   r.rec = static_cast<uint64_t*>(ws) + sv::kResHeadWords;
-  r.spin_limit = 1u << 20;  // about a second of polling, never reached (see the kernel)
-  const int64_t words = sv::kResHeadWords + int64_t{a.N} * a.K * p.G * sv::kResWords;
+  const int64_t recs = int64_t{a.N} * a.K * p.G * sv::kResWords;
+  r.state = reinterpret_cast<uint32_t*>(r.rec + recs);
+  r.first_polls = waits.first;
+  r.group_polls = waits.group;
+  r.next_group_polls = waits.next_group;
+  r.record_polls = waits.record;
+  r.hold = waits.hold;
+  // (the records take 48 of the 2048 bytes of indicator words per step and
+  // slice, the counters 64 and at most 8 a position)
+  const int64_t words = sv::kResHeadWords + recs + (p.groups + 1) / 2;
   hipLaunchKernelGGL(sv::fill_ones_kernel, dim3(static_cast<unsigned>(std::min<int64_t>((words + 255) / 256, 1024))),
                      dim3(sv::kThreads), 0, s, static_cast<uint64_t*>(ws), words);
   void (*k)(sv::TvArgs, sv::ResArgs) = sv::tv_resident_kernel<G, NV>;
   hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(p.groups * a.K * p.G)), dim3(sv::kResThreads), 0, s, a, r);
-  hipLaunchKernelGGL(sv::tv_resident_loss_kernel, dim3(1), dim3(sv::kThreads), 0, s, a,
-                     static_cast<const uint32_t*>(r.head));
+  void (*fin)(sv::TvArgs, sv::ResArgs) = sv::tv_resident_finish_kernel<G, NV>;
+  hipLaunchKernelGGL(fin, dim3(static_cast<unsigned>(std::min(a.N, kResFinishWgs))), dim3(sv::kResThreads), 0, s, a, r);
   *st = hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
   return true;
 }
 
 template <class E, int NT>
-spec_status launch_tv(const sv::TvArgs& a, void* res_ws, hipStream_t s) {
+spec_status launch_tv(const sv::TvArgs& a, void* res_ws, hipStream_t s, const ResWaits& waits) {
   spec_status st;
-  if (launch_tv_resident<E>(a, res_ws, s, &st)) return st;
+  if (launch_tv_resident<E>(a, res_ws, s, waits, &st)) return st;
   const int64_t units = int64_t{a.N} * a.K;
   const int C = a.rows.C;
   // the statistics per sub-chunk of kStep tiles with the wave-shaped pass,
@@ -936,11 +957,11 @@ spec_status spec_sample_gumbel(const void* logits, int64_t stride_r, spec_dtype 
   return dtype == SPEC_BF16 ? launch_sample_gumbel<BF16>(a, s) : launch_sample_gumbel<F32>(a, s);
 }
 
-spec_status spec_tv_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, int64_t t_stride_k,
-                                 const void* draft_logits, int64_t d_stride_n, int64_t d_stride_k,
-                                 spec_dtype dtype, int N, int K, int V, float temperature, spec_tv_mode mode,
-                                 float scale, float* loss, float* overlap, float* grad_draft, void* workspace,
-                                 size_t workspace_bytes, void* stream) {
+static spec_status tv_loss(const void* target_logits, int64_t t_stride_n, int64_t t_stride_k,
+                           const void* draft_logits, int64_t d_stride_n, int64_t d_stride_k,
+                           spec_dtype dtype, int N, int K, int V, float temperature, spec_tv_mode mode,
+                           float scale, float* loss, float* overlap, float* grad_draft, void* workspace,
+                           size_t workspace_bytes, void* stream, const ResWaits& waits) {
   if (dtype != SPEC_F32 && dtype != SPEC_BF16) return SPEC_EUNSUPPORTED;
   if (K > SPEC_MAX_K) return SPEC_EUNSUPPORTED;
   if (!tv_sizes_ok(N, K, V, dtype)) return SPEC_EINVAL;
@@ -982,7 +1003,36 @@ spec_status spec_tv_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, 
   a.bits_stride = static_cast<int64_t>(L.bits_stride);
   hipStream_t s = static_cast<hipStream_t>(stream);
   void* res_ws = ws + L.bits;  // the exchange records of the single-read pass, in the indicator words' place
-  return dtype == SPEC_BF16 ? launch_tv<BF16, kNtBf16>(a, res_ws, s) : launch_tv<F32, kNtF32>(a, res_ws, s);
+  return dtype == SPEC_BF16 ? launch_tv<BF16, kNtBf16>(a, res_ws, s, waits)
+                            : launch_tv<F32, kNtF32>(a, res_ws, s, waits);
+}
+
+spec_status spec_tv_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, int64_t t_stride_k,
+                                 const void* draft_logits, int64_t d_stride_n, int64_t d_stride_k,
+                                 spec_dtype dtype, int N, int K, int V, float temperature, spec_tv_mode mode,
+                                 float scale, float* loss, float* overlap, float* grad_draft, void* workspace,
+                                 size_t workspace_bytes, void* stream) {
+  return tv_loss(target_logits, t_stride_n, t_stride_k, draft_logits, d_stride_n, d_stride_k, dtype, N, K, V, temperature, mode,
+                 scale, loss, overlap, grad_draft, workspace, workspace_bytes, stream, ResWaits());
+}
+
+// Not part of the interface (specverify.h does not declare it): the TV loss with
+// the waits of its single-read pass given, for the tests of groups that give
+// up.  waits: the five members of ResWaits.
+spec_status spec_internal_tv_loss_waits(const void* target_logits, int64_t t_stride_n, int64_t t_stride_k,
+                                        const void* draft_logits, int64_t d_stride_n, int64_t d_stride_k,
+                                        spec_dtype dtype, int N, int K, int V, float temperature, spec_tv_mode mode,
+                                        float scale, float* loss, float* overlap, float* grad_draft, void* workspace,
+                                        size_t workspace_bytes, void* stream,
+                                        const unsigned* waits) {
+  ResWaits w;
+  w.first = waits[0];
+  w.group = waits[1];
+  w.next_group = waits[2];
+  w.record = waits[3];
+  w.hold = waits[4];
+  return tv_loss(target_logits, t_stride_n, t_stride_k, draft_logits, d_stride_n, d_stride_k, dtype, N, K, V, temperature, mode,
+                 scale, loss, overlap, grad_draft, workspace, workspace_bytes, stream, w);
 }
 
 size_t spec_verify_target_only_workspace_size(int B, int K, int V, spec_dtype dtype) {

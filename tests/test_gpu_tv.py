@@ -3,6 +3,8 @@ the C ABI): loss, per-step overlap and the gradient w.r.t. the draft logits
 for every loss mode, ragged vocabularies, forward-only calls and the
 full-size training workload (sampled positions plus a loss identity)."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -292,4 +294,49 @@ def test_single_read_two_streams():
     torch.cuda.synchronize()
     for o in outs[0] + outs[1]:
         for got, ref in zip(o, want):
+            assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("N,K,V,dtype", [
+    (70, 3, 100000, W.BF16),      # slices that exchange statistics
+    (300, 2, 30001, W.BF16),      # one slice a row, several positions a group
+    (40, 1, 8000, W.BF16),        # a group of one workgroup
+    (60, 3, 60001, W.F32),
+    (5, 8, 4 * 19 * 2048, W.F32),
+])
+@pytest.mark.parametrize("waits", [
+    (0, 0, 0, 1 << 20, 0xFFFFFFFF),   # every group but the first gives up
+    (0, 0, 0, 1 << 20, 1),            # every other group
+    (0, 0, 0, 1 << 20, 0),            # groups that are not complete at the first look
+    (1, 3, 1, 1 << 20, 0xFFFFFFFE),   # after a few looks: pairs of groups but the first
+    (0, 1 << 18, 256, 0, 0),          # complete groups whose records do not come: the loss is NaN
+])
+def test_single_read_groups_that_give_up(waits, N, K, V, dtype):
+    """Position groups that cannot wait for their workgroups (the waits' polls
+    are cut short, and whole groups never count as complete): the finish
+    launch computes their positions, the bits of the undisturbed call.  The
+    second call reuses the first one's workspace."""
+    d = W.tv_inputs_torch(N, K, V, dtype, 77, chunk=64)
+    tgt, drf = d["target"], d["draft"]
+    want = binding.tv_loss_fwd_bwd(tgt, drf, 0.9, "e2e", 0.5)
+    lib = binding.load_library()
+    call = lib.spec_internal_tv_loss_waits
+    call.argtypes = binding.TV_ARGTYPES + [ctypes.POINTER(ctypes.c_uint)]
+    ws = torch.empty(binding.tv_workspace_size(N, K, V, tgt.dtype), dtype=torch.uint8, device="cuda")
+    loss = torch.empty(1, device="cuda")
+    ov = torch.empty((N, K), device="cuda")
+    grad = torch.empty((N, K, V), device="cuda")
+    w = (ctypes.c_uint * 5)(*waits)
+    for _ in range(2):
+        for x in (loss, ov, grad):
+            x.fill_(7.0)
+        st = call(tgt.data_ptr(), tgt.stride(0), tgt.stride(1), drf.data_ptr(), drf.stride(0), drf.stride(1),
+                  binding.SPEC_BF16 if dtype == W.BF16 else binding.SPEC_F32, N, K, V, 0.9, 0, 0.5, loss.data_ptr(),
+                  ov.data_ptr(), grad.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream, w)
+        torch.cuda.synchronize()
+        assert st == 0
+        if waits[3] == 0:
+            assert torch.isnan(loss).all()
+            continue
+        for got, ref in zip((loss, ov, grad), want):
             assert torch.equal(got, ref)
