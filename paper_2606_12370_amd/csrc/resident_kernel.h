@@ -45,6 +45,7 @@ constexpr int kResWaves = kResThreads / 64;
 constexpr int kResMaxGroup = 40;   // workgroups of one position (K * G)
 constexpr int kResMaxSlices = 16;  // G
 constexpr int kResWords = 6;       // exchange words per slice: (m, D, D) and (alpha, S, 1 - S)
+constexpr int kResSumTiles = 16;   // tiles (of four elements a thread) that a float32 sum spans
 constexpr int kResHeadWords = 8;   // 64-bit words of counters before the records
 constexpr uint32_t kResGaveUp = 0x10000u;  // added to a group's arrivals (at most kResMaxGroup)
 
@@ -394,8 +395,10 @@ __device__ __forceinline__ bool res_position(const TvArgs& a, const ResArgs& r, 
   }
   __syncthreads();
   if (first && sh.fail) return false;  // (uniform; at a later position below)
-  float ap = 0.f, aq = 0.f, sc = 0.f;
+  // float32 over kResSumTiles tiles (64 elements) of a thread, float64 beyond
+  double sp = 0.0, sq = 0.0, sx = 0.0;
   {
+    float ap = 0.f, aq = 0.f, sc = 0.f;
     const float rt = res_uniform(sh.c[0]), rd = res_uniform(sh.c[1]), tau = res_uniform(sh.c[2]);
     const int jp = res_opaque_s(c.j0);
 #pragma unroll
@@ -415,10 +418,17 @@ __device__ __forceinline__ bool res_position(const TvArgs& a, const ResArgs& r, 
           o[i] = le ? eq : -eq;
         }
         res_put(xt[j], xd[j], o);
+        if ((NV - 1 - j) % kResSumTiles == 0) {
+          sp += static_cast<double>(ap);
+          sq += static_cast<double>(aq);
+          sx += static_cast<double>(sc);
+          ap = aq = sc = 0.f;
+        }
       }
   }
-  const double sp = wave_sum(static_cast<double>(ap)), sq = wave_sum(static_cast<double>(aq)),
-               sx = wave_sum(static_cast<double>(sc));
+  sp = wave_sum(sp);
+  sq = wave_sum(sq);
+  sx = wave_sum(sx);
   if (lane == 0) {
     sh.red[wave][0] = sp;
     sh.red[wave][1] = sq;

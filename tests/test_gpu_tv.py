@@ -340,3 +340,19 @@ def test_single_read_groups_that_give_up(waits, N, K, V, dtype):
             continue
         for got, ref in zip((loss, ov, grad), want):
             assert torch.equal(got, ref)
+
+
+def test_single_read_sums_of_a_dominant_token():
+    """Equal rows of one dominant token, first in its thread's sum, over a flat
+    tail whose terms t = 1.19e-8 are below half a unit in the last place of its
+    share, in calls of so many positions that a thread sums 152 elements.  The
+    overlap is 1; float32 sums of at most 64 elements lose at most 63 t =
+    7.5e-7 of it, less the 37 t that the normaliser's sums of 38 lose, plus the
+    rounding of the result (one sum of 152 is 1.35e-6 off)."""
+    N, V = 256, 38 * 2048
+    z = torch.zeros((N, 1, V), dtype=torch.bfloat16, device="cuda")
+    z[:, :, 0] = 18.25
+    loss, ov, grad = binding.tv_loss_fwd_bwd(z, z, 1.0, "per_step", 1.0)
+    torch.cuda.synchronize()
+    err = float((ov.double() - 1.0).abs().max())
+    assert err < 9e-7, err
