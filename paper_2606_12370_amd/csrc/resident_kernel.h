@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kResThreads, 2) void tv_resident_finish_kernel(TvAr
   const uint32_t flag = r.head[2], lost = r.head[3];
   double acc = 0.0;
   if (blockIdx.x == 0) acc = losses();  // (with the flags still on their way)
-  if (flag != 0u) {
+  if (__builtin_expect(flag != 0u, 1)) {
     if (blockIdx.x != 0) return;
   } else {
     for (int n = blockIdx.x; n < a.N; n += static_cast<int>(gridDim.x)) {

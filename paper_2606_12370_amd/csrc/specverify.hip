@@ -522,6 +522,25 @@ ResPlan res_plan(int N, int K, int V, int nv, int epv, int slots) {
   return p;
 }
 
+// Whether the passes that read the pair again take less time than the
+// single-read pass under plan p: calls of many positions over short rows, where
+// the single-read pass waits out its two exchanges at every position.  A
+// position takes a group 7 us and 0.68 a tile of its slice (float32 5.5 and
+// 0.78); the other passes take 13 us more in launches, then 12 ns a pair or
+// its 14 (float32 24) bytes an element at 5.6 (6.0) TB/s.  Measured, single
+// read / other passes, us a call, K = 3 bfloat16: V = 128, N = 512 56 / 39, N =
+// 4096 358 / 167; V = 4096, N = 64 18.5 / 26, N = 512 62 / 43, N = 4096 398 /
+// 197; V = 8192, N = 4096 478 / 283; V = 16384, N = 64 21 / 36, N = 512 86 /
+// 85, N = 4096 585 / 515; V = 32000, N = 64 25 / 44, N = 4096 861 / 1017;
+// float32 V = 4096, N = 512 53 / 44, V = 8192, N = 4096 398 / 415.
+bool res_short_rows(const ResPlan& p, int N, int K, int V, spec_dtype dt) {
+  const bool bf = dt == SPEC_BF16;
+  const double rounds = static_cast<double>(N) / p.groups, slice = (p.tiles + p.G - 1) / p.G;
+  const double single = rounds * (bf ? 7.0 + 0.68 * slice : 5.5 + 0.78 * slice);
+  const double other = 13.0 + static_cast<double>(N) * K * std::max(0.012, V * (bf ? 2.5e-6 : 4.0e-6));
+  return other < single;
+}
+
 // Polls of the waits (about a microsecond each): 64 before a workgroup looks at
 // its group at all; a quarter of a second for the group to become complete
 // (as long as a call that fills the card's memory holds the device); once a
@@ -545,7 +564,7 @@ bool launch_tv_resident(const sv::TvArgs& a, void* ws, hipStream_t s, const ResW
   const ResFacts* f = res_facts();
   if (!f || f->slots[dt] <= 0) return false;
   const ResPlan p = res_plan(a.N, a.K, d.V, NV, G::EPV, f->slots[dt]);
-  if (p.G == 0) return false;
+  if (p.G == 0 || res_short_rows(p, a.N, a.K, d.V, dt)) return false;
   sv::ResArgs r;
   r.G = p.G;
   r.tiles = p.tiles;

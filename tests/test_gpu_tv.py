@@ -187,6 +187,30 @@ def test_single_read_edges(N, K, V, dtype, mode):
 
 
 @pytest.mark.parametrize("mode", ["e2e", "prod", "per_step"])
+@pytest.mark.parametrize("N,K,V,dtype", [
+    (1500, 3, 4097, W.BF16),      # so many positions of short rows that the passes that read twice take them
+    (2000, 2, 1023, W.F32),
+    (4096, 1, 16384, W.BF16),
+    (70, 3, 4097, W.BF16),        # short rows of few positions: the single-read pass
+    (500, 3, 32000, W.BF16),      # many positions of longer rows: the single-read pass
+])
+def test_short_rows(N, K, V, dtype, mode):
+    """Either side of the rule that sends calls of many positions over short
+    rows to the passes that read twice: sampled positions against the oracle."""
+    d = W.tv_inputs_torch(N, K, V, dtype, 31, chunk=64)
+    loss, ov, grad = binding.tv_loss_fwd_bwd(d["target"], d["draft"], 0.8, mode, 0.5)
+    torch.cuda.synchronize()
+    pos = np.unique(np.linspace(0, N - 1, 6).astype(int))
+    pi = torch.as_tensor(pos, device="cuda")
+    ref = oracle.tv_ref(host_logits(d["target"][pi], dtype), host_logits(d["draft"][pi], dtype),
+                        float(np.float32(0.8)), MODES[mode], 0.5, want_grad=True)
+    ref["scale"] = 0.5
+    compare_tv(loss, ov, grad, ref, dtype, positions=pos, loss_exact=False)
+    total = 0.5 * chain_factors(ov.cpu().numpy().astype(np.float64), MODES[mode])[1].sum()
+    assert abs(float(loss) - total) <= 1e-5 * abs(total) + 1e-6 * N * K
+
+
+@pytest.mark.parametrize("mode", ["e2e", "prod", "per_step"])
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
 @pytest.mark.parametrize("V,first,count,masked", [
     (2048, 0, 4, False), (2052, 2048, 4, False),    # every logit one thread holds
