@@ -613,20 +613,25 @@ __global__ __launch_bounds__(kThreads) void kl_coef_kernel(KlArgs a) {
 // sign(d) |q - p| scale / (K T), d = log2 q - log2 p formed with the
 // pairwise partition-function ratio of kl_coef.  Reverse KL: scale / (K T)
 // q ln2 ((d - c) - (mu - c)).
-template <class E, int NT, int S, int KIND>
-__global__ __launch_bounds__(kThreads) void kl_grad_kernel(KlArgs a, int64_t nitems, int per_pair) {
+// Waves per SIMD that the registers are to leave room for.
+template <class E, int KIND, bool PAIR>
+constexpr int kKlGradWaves = std::is_same<E, F32>::value || (KIND != kKlReverse && !PAIR) ? 7 : 8;
+template <class E, int NT, int S, int KIND, bool PAIR>
+__global__ __launch_bounds__(kThreads, (kKlGradWaves<E, KIND, PAIR>)) void kl_grad_kernel(KlArgs a, int64_t nitems) {
   constexpr int EPV = E::EPV;
   constexpr int TILE = kThreads * EPV;
-  // One workgroup per chunk, or (per_pair, large forward-KL / CE calls) per
+  // One workgroup per chunk, or (PAIR, large forward-KL / CE calls) per
   // (position, step) pair, its chunks in turn, since every pair beyond the
-  // pair limit leaves at once.
+  // pair limit leaves at once.  (PAIR chosen at run time took 66 registers instead
+  // of 63 for reverse KL and 71 instead of 64 for the pairs, a wave per SIMD
+  // less.)
   const RowsDesc& d = a.rows;
   const int C = a.PC, V = d.V, NK = a.N * a.K;
   const float gcoef = static_cast<float>(a.scale * static_cast<double>(a.inv_t) / a.K);
   for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int u = per_pair ? static_cast<int>(it) : static_cast<int>(it / C);
-    const int c0 = per_pair ? 0 : static_cast<int>(it - static_cast<int64_t>(u) * C);
-    const int c1 = per_pair ? C : c0 + 1;
+    const int u = PAIR ? static_cast<int>(it) : static_cast<int>(it / C);
+    const int c0 = PAIR ? 0 : static_cast<int>(it - static_cast<int64_t>(u) * C);
+    const int c1 = PAIR ? C : c0 + 1;
     int bb;
     const typename E::raw* rt = row_of<E>(d, u, &bb);
     const typename E::raw* rd = row_of<E>(d, NK + u, &bb);

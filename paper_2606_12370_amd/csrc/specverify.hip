@@ -684,10 +684,14 @@ spec_status launch_kl(const sv::KlArgs& a, hipStream_t s) {
     // limit are left to write): one per pair in the largest calls, where the
     // workgroups that leave at once would cost more than the last one that
     // walks its pair alone (100 us at V = 151936)
-    void (*kg)(sv::KlArgs, int64_t, int) = sv::kl_grad_kernel<G, CHUNK / (sv::kThreads * G::EPV), kStep, KIND>;
-    const int per_pair = KIND != sv::kKlReverse && units * C > kKlPairTasks ? 1 : 0;
-    const int64_t grid = per_pair ? units : units * C;
-    hipLaunchKernelGGL(kg, dim3(static_cast<unsigned>(grid)), dim3(sv::kThreads), 0, s, a, grid, per_pair);
+    constexpr int NTG = CHUNK / (sv::kThreads * G::EPV);
+    bool pair = false;
+    if constexpr (KIND != sv::kKlReverse && CHUNK == kChunkElems) pair = units * C > kKlPairTasks;
+    void (*kg)(sv::KlArgs, int64_t) = sv::kl_grad_kernel<G, NTG, kStep, KIND, false>;
+    if constexpr (KIND != sv::kKlReverse && CHUNK == kChunkElems)
+      if (pair) kg = sv::kl_grad_kernel<G, NTG, kStep, KIND, true>;
+    const int64_t grid = pair ? units : units * C;
+    hipLaunchKernelGGL(kg, dim3(static_cast<unsigned>(grid)), dim3(sv::kThreads), 0, s, a, grid);
   }
   hipLaunchKernelGGL(sv::kl_loss_kernel, dim3(1), dim3(sv::kThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;
