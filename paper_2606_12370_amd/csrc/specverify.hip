@@ -630,9 +630,14 @@ spec_status launch_tv(const sv::TvArgs& a, void* res_ws, hipStream_t s, const Re
 // N = 8, K = 3, V = 151936 bfloat16 55.9 / 47.4; N = 64, V = 65536 69.8 /
 // 64.9; N = 300, K = 2, V = 50000 float32 173.5 / 163.3; N = 270, K = 3,
 // V = 151936 (8100 tasks) 368.7 / 359.4; N = 2048 2606 / 2626.  Without a
-// gradient: 2400 tasks 101.4 / 98.1, 6000 145.3 / 149.6.
+// gradient (K = 1 to 3, V = 32000 to 262144) forward KL and CE gain up to about
+// 2000 tasks (512 38.9 / 33.1, 1920 67.5 / 66.1, 3072 96.7 / 98.2, 4096 119.1 /
+// 122.4; float32 1280 74.4 / 70.1, 2048 102.7 / 104.8), reverse KL, whose pass
+// reads twice as wide, up to about 700 (384 41.1 / 39.4, 640 43.2 / 42.7, 1024
+// 50.0 / 51.7, 3072 94.6 / 96.8).
 constexpr int64_t kKlSmallTasks = 8192;
-constexpr int64_t kKlSmallTasksForward = 4096;
+constexpr int64_t kKlSmallTasksNoGrad = 1536;
+constexpr int64_t kKlSmallTasksNoGradReverse = 700;
 // Tasks beyond which the forward-KL / CE gradient pass takes a workgroup per
 // pair instead of one per chunk (forward KL, K = 3, V = 151936 bfloat16, us a
 // call): N = 200 312 / 229, N = 300 410 / 334, N = 2048 (61440 tasks) 2115 /
@@ -1224,7 +1229,9 @@ spec_status spec_kl_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, 
   a.norms = reinterpret_cast<sv::KlNorm*>(ws + L.norms);
   // the partial sums per chunk; twice as many fit in the statistics' place,
   // which nothing reads once the pass runs
-  const bool small = int64_t{N} * K * g.C <= (grad_draft ? kKlSmallTasks : kKlSmallTasksForward);
+  const int64_t small_tasks =
+      grad_draft ? kKlSmallTasks : (kind == SPEC_KL_REVERSE ? kKlSmallTasksNoGradReverse : kKlSmallTasksNoGrad);
+  const bool small = int64_t{N} * K * g.C <= small_tasks;
   const int chunk = small ? kChunkElems / 2 : kChunkElems;
   a.PC = (V + chunk - 1) / chunk;
   a.parts = reinterpret_cast<sv::KlPart*>(ws + (small ? L.stats : L.parts));

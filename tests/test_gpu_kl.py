@@ -207,6 +207,10 @@ def test_target_masked_tokens_forward_and_ce(dtype):
     (257, 2, 16384 * 15 + 9, W.BF16),   # the larger chunks, gradient pass by chunk
     (1200, 4, 16385, W.F32),            # the same, two chunks a row
     (50100, 2, 128, W.BF16),            # gradient pass by pair
+    (256, 3, 16384 + 9, W.BF16),        # without a gradient: the most tasks with the smaller chunks,
+    (257, 3, 16384 + 9, W.F32),         # the larger ones,
+    (175, 2, 16384 + 8200, W.BF16),     # and the same for reverse KL
+    (176, 2, 16384 + 8200, W.BF16),
 ])
 def test_chunk_rules(N, K, V, dtype, kind):
     """Either side of the sizes where the passes change their chunks and the
