@@ -730,6 +730,7 @@ spec_status launch_sample(const sv::SampleArgs& a, hipStream_t s) {
 
 // Diagnostics per sub-chunk of kStep tiles, one wave per sub-chunk in the
 // statistics, one workgroup in the pair pass.
+constexpr int64_t kMaxGridX = (int64_t{1} << 24) - 1;
 template <class E>
 spec_status launch_diag(const sv::DiagArgs& a, hipStream_t s) {
   const int C = a.rows.C;
@@ -740,8 +741,11 @@ spec_status launch_diag(const sv::DiagArgs& a, hipStream_t s) {
                      a.rows, const_cast<sv::DiagStat*>(a.stats), nsub);
   hipLaunchKernelGGL(sv::diag_norm_kernel, dim3(static_cast<unsigned>((2 * units + sv::kWaves - 1) / sv::kWaves)),
                      dim3(sv::kThreads), 0, s, a.stats, static_cast<int>(2 * units), C, a.norms, a.info);
-  hipLaunchKernelGGL((sv::diag_pair_kernel<E, kStep, kDiagPairVec>), dim3(static_cast<unsigned>(units * C)),
-                     dim3(sv::kThreads), 0, s, a);
+  // (a launch holds fewer than 2^32 threads along x: more items go along y)
+  const int64_t items = units * C, across = std::min(items, kMaxGridX);
+  hipLaunchKernelGGL((sv::diag_pair_kernel<E, kStep, kDiagPairVec>),
+                     dim3(static_cast<unsigned>(across), static_cast<unsigned>((items + across - 1) / across)),
+                     dim3(sv::kThreads), 0, s, a, items);
   hipLaunchKernelGGL((sv::diag_finish_kernel<E>), dim3(static_cast<unsigned>((units + sv::kWaves - 1) / sv::kWaves)),
                      dim3(sv::kThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_EHIP;

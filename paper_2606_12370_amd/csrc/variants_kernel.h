@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kThreads) void diag_stats_wave_kernel(RowsDesc d, D
 // 62.8 / 56.3, B = 256 167.1 / 162.3, B = 700 422.5 / 417.6; four vectors per
 // load step 163.5 at B = 256.)
 template <class E, int ST, int S>
-__global__ __launch_bounds__(kThreads) void diag_pair_kernel(DiagArgs a) {
+__global__ __launch_bounds__(kThreads) void diag_pair_kernel(DiagArgs a, int64_t nitems) {
   constexpr int EPV = E::EPV;
   constexpr int WV = ST * (kThreads / 64);
   constexpr int NW = WV / S / kWaves;  // load steps per wave
@@ -447,7 +447,8 @@ __global__ __launch_bounds__(kThreads) void diag_pair_kernel(DiagArgs a) {
   const RowsDesc& d = a.rows;
   const int C = d.C, BK = a.B * a.K;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t g = static_cast<int64_t>(blockIdx.x);
+  const int64_t g = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+  if (g >= nitems) return;
   const int u = static_cast<int>(g / C), j = static_cast<int>(g - static_cast<int64_t>(g / C) * C);
   int b;
   const typename E::raw* rt = row_of<E>(d, u, &b);

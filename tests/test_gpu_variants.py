@@ -333,3 +333,21 @@ def test_diagnostics_benchmark_batch_sampled_rows():
                           d["temperature"][ri].cpu().numpy().astype(np.float64))
     rep = compare_diagnostics(out, ref, W.BF16, rows=rows)
     print(rep, "mean alpha_rs", float(out["alpha_rs"].mean()), "mean alpha_to", float(out["alpha_to"].mean()))
+
+
+def test_diagnostics_of_more_items_than_a_grid_row():
+    """2^24 + 8 (step, sub-chunk) items, more workgroups than a launch holds
+    along one dimension: accepted, and every table entry that of the same call
+    in two halves."""
+    B, K, V = (1 << 21) + 1, 8, 3
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    tgt = torch.randn((B, K, V), device="cuda", generator=g)
+    drf = torch.randn((B, K, V), device="cuda", generator=g)
+    out = binding.diagnostics(tgt, drf, 0.9)
+    h = B // 2
+    for sl in (slice(0, h), slice(h, B)):
+        part = binding.diagnostics(tgt[sl], drf[sl], 0.9)
+        torch.cuda.synchronize()
+        for name in ("table", "greedy_draft", "rs_preferred"):
+            assert torch.equal(out[name][sl], part[name])
