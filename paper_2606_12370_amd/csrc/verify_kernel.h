@@ -676,9 +676,17 @@ __device__ __forceinline__ int tile_masses(const typename E::raw* rt, const type
 #pragma unroll
   for (int j0 = 0; j0 < NT; j0 += S) {
     if (j0 >= nt_tiles) break;
+    // (RawSpan, not load_tiles: with the short rows' loads on a path of their
+    // own finish_kernel spills 62 scalar registers instead of 2 and
+    // sample_kernel takes 74 vector registers instead of 72, six waves per
+    // SIMD instead of seven)
     float xt[S][EPV], xd[S][EPV];
-    load_tiles<E, S>(rt, tile0 + j0, V, xt);
-    if (residual) load_tiles<E, S>(rd, tile0 + j0, V, xd);
+    const int es = (tile0 + j0) * TILE, t = static_cast<int>(threadIdx.x);
+    RawSpan<E, S, kThreads> wt, wd;
+    wt.issue(rt, es, t, V);
+    if (residual) wd.issue(rd, es, t, V);
+    wt.expand(rt, es, t, V, xt);
+    if (residual) wd.expand(rd, es, t, V, xd);
 #pragma unroll
     for (int j = 0; j < S; ++j)
 #pragma unroll
