@@ -66,9 +66,12 @@ constexpr int64_t kDecidePairItems = 768;
 // Residual-step items up to which the pair pass takes them first: about the
 // items the device holds at once in each shape (one workgroup per item,
 // residual items first against the pair order: 1216 residual items 65.8 /
-// 66.4 us, 2432 102.3 / 100.8, 4864 178.3 / 174.2; one wave per item: 4864
-// 177.5 / 187.1, 24576 1103 / 1074).
+// 66.4 us, 2432 102.3 / 100.8, 4864 178.3 / 174.2; with float32 logits, whose
+// items are half as long, V = 32000, K = 3, B = 256 (2048 residual items) 82.7 /
+// 84.1, B = 512 147.5 / 151.2, B = 1024 (8192) 280.4 / 283.6; one wave per item:
+// 4864 177.5 / 187.1, 24576 1103 / 1074).
 constexpr int64_t kLongestFirstShared = 1536;
+constexpr int64_t kLongestFirstSharedF32 = 8192;
 constexpr int64_t kLongestFirstItems = 8192;
 constexpr int kDiagPairVec = 2;
 // (4 vectors per load step for the diagnostics statistics: 166.5-167.5
@@ -395,7 +398,8 @@ spec_status launch_verify(const sv::VerifyArgs& a, int64_t rows, hipStream_t s, 
   // device holds at once, else the pair order (without overlaps every item
   // is a residual-step item)
   const int64_t first = int64_t{a.B} * a.rows.C;
-  const int longest_first = (a.overlap == nullptr || first <= (split ? kLongestFirstShared : kLongestFirstItems)) ? 1 : 0;
+  const int64_t shared_first = std::is_same<E, F32>::value ? kLongestFirstSharedF32 : kLongestFirstShared;
+  const int longest_first = (a.overlap == nullptr || first <= (split ? shared_first : kLongestFirstItems)) ? 1 : 0;
   if (split)
     hipLaunchKernelGGL((sv::pair_pass_wave_kernel<E, kStep, kPairVec, true>), dim3(static_cast<unsigned>(items)),
                        dim3(sv::kThreads), 0, s, a, items, longest_first);
