@@ -460,10 +460,16 @@ __device__ __forceinline__ bool res_position(const TvArgs& a, const ResArgs& r, 
         S += sh.x[(lane * G + i) * 3 + 1];
         Sc += sh.x[(lane * G + i) * 3 + 2];
       }
+    // the draft's probabilities normalised by their own sum, S + (1 - S): the
+    // errors of the exponentials they share fall out
+    const double qn = 1.0 / (S + Sc);
+    al = (al - S) + S * qn;
+    S *= qn;
+    Sc *= qn;
     double gk, L;
     chain_factor_of(K, a.mode, c.k, [&](int i) -> double { return dpp::lane(al, i); }, &gk, &L);
-    gk = a.scale * gk * static_cast<double>(a.inv_t);
-    const double A1 = gk * dpp::lane(Sc, c.k) * sh.cc[1], A0 = -gk * dpp::lane(S, c.k) * sh.cc[1];
+    gk = a.scale * gk * static_cast<double>(a.inv_t) * dpp::lane(qn, c.k) * sh.cc[1];
+    const double A1 = gk * dpp::lane(Sc, c.k), A0 = -gk * dpp::lane(S, c.k);
     if (lane == 0) {
       sh.c[4] = static_cast<float>(A1);
       sh.c[5] = static_cast<float>(A0);
