@@ -81,9 +81,8 @@ struct GumbelBest {  // one part of the emitting row
 // 107 us a call in bfloat16, 231 -> 127 in float32; rows with one token 22
 // above the rest 153 -> 87; Gumbel-max verification at B = 256, K = 3 258 ->
 // 207 with overlaps, 183 -> 145 without.
-constexpr int kScanBlocks = 1;                        // blocks per lane and load step
-constexpr int kScanQueue = 64 + 64 * kScanBlocks;     // queue entries per wave
-constexpr int kScanTile = kThreads * 8;               // elements per workgroup and block
+constexpr int kScanQueue = 128;          // queue entries per wave: a step adds up to 64 to fewer than 64
+constexpr int kScanTile = kThreads * 8;  // elements per workgroup and step, a block per lane
 constexpr float kVarMax = 25.01f;                     // -log2 E < 25 + 1e-7
 
 // t with 2 t <= 1 - U (0 where the bound says nothing): f = 1/2 + the top 23
@@ -187,88 +186,78 @@ __device__ __forceinline__ void gumbel_scan(const typename E::raw* rx, const typ
   bool isbad = false;
   int qn = 0;  // entries of this wave's queue
   const bool vec = V >= 8;
-  constexpr int STEP = kScanTile * kScanBlocks;
-  Block8<E> nx[kScanBlocks], ny[kScanBlocks];
+  Block8<E> nx, ny;
   auto load = [&](int es) {
-#pragma unroll
-    for (int j = 0; j < kScanBlocks; ++j) {
-      const int v0 = es + j * kScanTile + static_cast<int>(threadIdx.x) * 8;
-      nx[j].load(rx, v0 < e1 ? v0 : V, V);
-      if (BOTH) ny[j].load(ry, v0 < e1 ? v0 : V, V);
-    }
+    const int v0 = es + static_cast<int>(threadIdx.x) * 8;
+    nx.load(rx, v0 < e1 ? v0 : V, V);
+    if (BOTH) ny.load(ry, v0 < e1 ? v0 : V, V);
   };
   if (vec && e0 < e1) load(e0);
   if (threadIdx.x == 0)
     sh.best = row_best ? __hip_atomic_load(row_best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : key_order(Key::kNone);
   __syncthreads();
-  for (int es = e0; es < e1; es += STEP) {
-    const bool last = es + STEP >= e1;
+  for (int es = e0; es < e1; es += kScanTile) {
+    const bool last = es + kScanTile >= e1;
     float thr = key_unorder(__hip_atomic_load(&sh.best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
     key.set(thr);
-    Block8<E> wx[kScanBlocks], wy[kScanBlocks];
+    Block8<E> wx, wy;
     if (vec) {  // this step's blocks, and the loads of the next step's behind them
-#pragma unroll
-      for (int j = 0; j < kScanBlocks; ++j) {
-        wx[j] = nx[j];
-        if (BOTH) wy[j] = ny[j];
-      }
-      if (!last) load(es + STEP);
+      wx = nx;
+      if (BOTH) wy = ny;
+      if (!last) load(es + kScanTile);
     }
-#pragma unroll
-    for (int j = 0; j < kScanBlocks; ++j) {
-      const int v0 = es + j * kScanTile + static_cast<int>(threadIdx.x) * 8;
-      float x[8], y[8], r[8];
-      if (vec && v0 + 8 <= V) {
-        wx[j].widen(x);
-        if (BOTH) wy[j].widen(y);
-      } else {
-        block_elements<E>(rx, v0, V, x);
-        if (BOTH) block_elements<E>(ry, v0, V, y);
-      }
-      weight(x, y, r);
-      float mx = r[0];
-#pragma unroll
-      for (int k = 1; k < 8; ++k) mx = max_nan(mx, r[k]);
-      if (Key::kLogits && !(mx < INFINITY)) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) isbad |= !(x[k] < INFINITY);
-      }
-      const bool need = v0 < e1 && v0 < V && key.block(mx);
-      const uint64_t m = __ballot(need);
-      if (need) {
-        const int at = qn + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                static_cast<uint32_t>(m >> 32),
-                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
-#pragma unroll
-        for (int k = 0; k < 8; ++k) sh.q[wave][k][at] = r[k];
-        sh.qv[wave][at] = v0;
-      }
-      qn += __popcll(m);
+    const int v0 = es + static_cast<int>(threadIdx.x) * 8;
+    float x[8], y[8], r[8];
+    if (vec && v0 + 8 <= V) {
+      wx.widen(x);
+      if (BOTH) wy.widen(y);
+    } else {
+      block_elements<E>(rx, v0, V, x);
+      if (BOTH) block_elements<E>(ry, v0, V, y);
     }
+    weight(x, y, r);
+    float mx = r[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) mx = max_nan(mx, r[k]);
+    if (Key::kLogits && !(mx < INFINITY)) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) isbad |= !(x[k] < INFINITY);
+    }
+    const bool need = v0 < e1 && v0 < V && key.block(mx);
+    const uint64_t m = __ballot(need);
+    if (need) {
+      const int at = qn + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                              static_cast<uint32_t>(m >> 32),
+                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) sh.q[wave][k][at] = r[k];
+      sh.qv[wave][at] = v0;
+    }
+    qn += __popcll(m);
     while (qn >= 64 || (last && qn > 0)) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       const int first = qn >= 64 ? qn - 64 : 0;
       const bool on = first + lane < qn;
       const int at = on ? first + lane : first;
-      const int v0 = sh.qv[wave][at];
-      float r[8];
+      const int vq = sh.qv[wave][at];
+      float rq[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = sh.q[wave][k][at];
+      for (int k = 0; k < 8; ++k) rq[k] = sh.q[wave][k][at];
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       qn = first;
-      const Philox4x64 g = philox4x64_10(c0, static_cast<uint64_t>(static_cast<uint32_t>(v0) >> 3), c2, tag, seed, 0ull);
-      float mx = key.bound(r[0], var_bound(g, 0));
+      const Philox4x64 g = philox4x64_10(c0, static_cast<uint64_t>(static_cast<uint32_t>(vq) >> 3), c2, tag, seed, 0ull);
+      float mq = key.bound(rq[0], var_bound(g, 0));
 #pragma unroll
-      for (int k = 1; k < 8; ++k) mx = max_nan(mx, key.bound(r[k], var_bound(g, k)));
-      const bool cand = on && key.reaches(mx);
+      for (int k = 1; k < 8; ++k) mq = max_nan(mq, key.bound(rq[k], var_bound(g, k)));
+      const bool cand = on && key.reaches(mq);
       if (__ballot(cand) != 0) {
         if (cand) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
-            const float kk = Key::key(r[k], exp_variate(g, k));
-            const bool better = Key::counts(r[k]) & ((kk > bk) | ((kk == bk) & (v0 + k < bi)));
+            const float kk = Key::key(rq[k], exp_variate(g, k));
+            const bool better = Key::counts(rq[k]) & ((kk > bk) | ((kk == bk) & (vq + k < bi)));
             bk = better ? kk : bk;
-            bi = better ? v0 + k : bi;
+            bi = better ? vq + k : bi;
           }
         }
         const float wb = wave_max(bk);

@@ -330,7 +330,7 @@ const FusedFacts* fused_facts() {
 int fused_capacity(const sv::VerifyArgs& a, spec_dtype dt) {
   const int G = slices(a.rows.V, dt);
   const int epv = dt == SPEC_BF16 ? sv::BF16::EPV : sv::F32::EPV;
-  if (a.K < 1 || a.K > kFusedMaxK || !a.rows.vec_t || !a.rows.vec_d || G > 64 || a.rows.V % epv != 0) return 0;
+  if (a.K < 1 || a.K > kFusedMaxK || !a.vec_rows || G > 64 || a.rows.V % epv != 0) return 0;
   const FusedFacts* f = fused_facts();
   if (!f || !f->coop || f->cus <= 0) return 0;
   const int cap = f->bpc[dt][a.K] * f->cus;
@@ -786,8 +786,8 @@ spec_status prepare_verify(const void* target_logits, int64_t t_stride_b, int64_
   a.rows.nb = B;
   a.rows.temp = temperature; a.rows.temp_scalar = temperature_scalar;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = gumbel ? g.C : sub_chunks(V, dtype);
-  a.rows.vec_t = rows_vec_aligned(target_logits, t_stride_b, t_stride_k, es) ? 1 : 0;
-  a.rows.vec_d = rows_vec_aligned(draft_logits, d_stride_b, d_stride_k, es) ? 1 : 0;
+  a.vec_rows = rows_vec_aligned(target_logits, t_stride_b, t_stride_k, es) &&
+               rows_vec_aligned(draft_logits, d_stride_b, d_stride_k, es);
   a.B = B; a.K = K;
   a.ids = draft_ids;
   a.seed = seed; a.offset = offset;
@@ -983,8 +983,6 @@ spec_status spec_sample_gumbel(const void* logits, int64_t stride_r, spec_dtype 
   a.rows.nb = R;
   a.rows.temp = temperature; a.rows.temp_scalar = temperature_scalar;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = g.C;
-  a.rows.vec_t = rows_vec_aligned(logits, stride_r, 0, esize_of(dtype)) ? 1 : 0;
-  a.rows.vec_d = 0;
   a.R = R;
   a.seed = seed; a.offset = offset;
   a.token = tokens;
@@ -1015,15 +1013,12 @@ static spec_status tv_loss(const void* target_logits, int64_t t_stride_n, int64_
   if (!aligned16(workspace)) return SPEC_EINVAL;
 
   const Geometry g = geometry(V, dtype);
-  const size_t es = esize_of(dtype);
   sv::TvArgs a{};
   a.rows.tgt = target_logits; a.rows.tsb = t_stride_n; a.rows.tsk = t_stride_k; a.rows.tper = K;
   a.rows.drf = draft_logits; a.rows.dsb = d_stride_n; a.rows.dsk = d_stride_k; a.rows.dper = K;
   a.rows.nb = N;
   a.rows.temp = nullptr; a.rows.temp_scalar = temperature;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = g.C;
-  a.rows.vec_t = rows_vec_aligned(target_logits, t_stride_n, t_stride_k, es) ? 1 : 0;
-  a.rows.vec_d = rows_vec_aligned(draft_logits, d_stride_n, d_stride_k, es) ? 1 : 0;
   a.N = N; a.K = K;
   a.mode = static_cast<int>(mode);
   a.scale = static_cast<double>(scale);
@@ -1100,8 +1095,6 @@ spec_status spec_verify_target_only(const void* target_logits, int64_t t_stride_
   a.rows.nb = B;
   a.rows.temp = temperature; a.rows.temp_scalar = temperature_scalar;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = sub_chunks(V, dtype);
-  a.rows.vec_t = rows_vec_aligned(target_logits, t_stride_b, t_stride_k, esize_of(dtype)) ? 1 : 0;
-  a.rows.vec_d = 0;
   a.B = B; a.K = K;
   a.ids = draft_ids;
   a.seed = seed; a.offset = offset;
@@ -1135,8 +1128,6 @@ spec_status spec_sample(const void* logits, int64_t stride_r, spec_dtype dtype, 
   a.rows.nb = R;
   a.rows.temp = temperature; a.rows.temp_scalar = temperature_scalar;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = sub_chunks(V, dtype);
-  a.rows.vec_t = rows_vec_aligned(logits, stride_r, 0, esize_of(dtype)) ? 1 : 0;
-  a.rows.vec_d = 0;
   a.R = R;
   a.seed = seed; a.offset = offset;
   a.token = tokens; a.logz = logz;
@@ -1170,15 +1161,12 @@ spec_status spec_diagnostics(const void* target_logits, int64_t t_stride_b, int6
   if (!aligned16(workspace)) return SPEC_EINVAL;
 
   const Geometry g = geometry(V, dtype);
-  const size_t es = esize_of(dtype);
   sv::DiagArgs a{};
   a.rows.tgt = target_logits; a.rows.tsb = t_stride_b; a.rows.tsk = t_stride_k; a.rows.tper = K;
   a.rows.drf = draft_logits; a.rows.dsb = d_stride_b; a.rows.dsk = d_stride_k; a.rows.dper = K;
   a.rows.nb = B;
   a.rows.temp = temperature; a.rows.temp_scalar = temperature_scalar;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = sub_chunks(V, dtype);
-  a.rows.vec_t = rows_vec_aligned(target_logits, t_stride_b, t_stride_k, es) ? 1 : 0;
-  a.rows.vec_d = rows_vec_aligned(draft_logits, d_stride_b, d_stride_k, es) ? 1 : 0;
   a.B = B; a.K = K;
   a.out = diag; a.greedy = greedy_draft; a.prefer = rs_preferred;
   char* ws = static_cast<char*>(workspace);
@@ -1217,15 +1205,12 @@ spec_status spec_kl_loss_fwd_bwd(const void* target_logits, int64_t t_stride_n, 
   if (!aligned16(workspace)) return SPEC_EINVAL;
 
   const Geometry g = geometry(V, dtype);
-  const size_t es = esize_of(dtype);
   sv::KlArgs a{};
   a.rows.tgt = target_logits; a.rows.tsb = t_stride_n; a.rows.tsk = t_stride_k; a.rows.tper = K;
   a.rows.drf = draft_logits; a.rows.dsb = d_stride_n; a.rows.dsk = d_stride_k; a.rows.dper = K;
   a.rows.nb = N;
   a.rows.temp = nullptr; a.rows.temp_scalar = temperature;
   a.rows.V = V; a.rows.ntiles = g.ntiles; a.rows.C = g.C;
-  a.rows.vec_t = rows_vec_aligned(target_logits, t_stride_n, t_stride_k, es) ? 1 : 0;
-  a.rows.vec_d = rows_vec_aligned(draft_logits, d_stride_n, d_stride_k, es) ? 1 : 0;
   a.N = N; a.K = K;
   a.kind = static_cast<int>(kind);
   a.scale = static_cast<double>(scale);

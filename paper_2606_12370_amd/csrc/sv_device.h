@@ -494,7 +494,6 @@ struct RowsDesc {
   int nb;
   const float* temp; float temp_scalar;  // per batch row, or one scalar (temp == nullptr)
   int V, ntiles, C;
-  int vec_t, vec_d;
 };
 
 template <class E>

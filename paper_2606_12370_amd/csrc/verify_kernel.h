@@ -125,6 +125,7 @@ struct VerifyArgs {
   int32_t* decision;      // [B]: accept length n, or -1 for a row with a data error
   PairStat* pairs;        // [B*K][C]
   int want_z;             // pair_pass also sums the residual mass of the first rejected step
+  bool vec_rows;          // every row is 16-byte aligned (the single-read path needs it)
 };
 
 __device__ __forceinline__ int target_row(const VerifyArgs& a, int b, int i) { return b * (a.K + 1) + i; }
