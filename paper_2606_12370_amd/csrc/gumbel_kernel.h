@@ -391,22 +391,23 @@ __global__ __launch_bounds__(kThreads) void gumbel_finish_kernel(VerifyArgs a, c
 // ---------------------------------------------------------------------------
 // Gumbel-max draft sampler
 
+struct SampleBest {  // one part of a row
+  float k;           // best key (-inf: none)
+  int i;             // its first index (kNoIndex: none), or -1 for a data error in the part
+};
+
 struct GumbelSampleArgs {
   RowsDesc rows;  // tper = 1, nb = R rows
   int R;
   uint64_t seed, offset;
   int32_t* token;
-  GumbelBest* best;  // [R][P]: kr = best score, ir = its index, ip = data-error flag
+  SampleBest* best;  // [R][P]
   int P;             // parts per row
-  int share;         // kp of a row's part 0 holds the row's best key so far
+  int* row_best;     // [R]: the row's best key so far, as key_order (null: not shared)
 };
-
-__device__ __forceinline__ int* row_best_of(const GumbelSampleArgs& a, int r) {
-  return reinterpret_cast<int*>(&a.best[static_cast<int64_t>(r) * a.P].kp);
-}
 __global__ __launch_bounds__(kThreads) void gumbel_sample_init_kernel(GumbelSampleArgs a) {
   const int r = blockIdx.x * kThreads + threadIdx.x;
-  if (r < a.R) *row_best_of(a, r) = key_order(KeyScore::kNone);
+  if (r < a.R) a.row_best[r] = key_order(KeyScore::kNone);
 }
 
 // One workgroup per (row, part).  A greedy row (T = 0) compares its logits.
@@ -457,11 +458,13 @@ __global__ __launch_bounds__(kThreads) void gumbel_sample_pass_kernel(GumbelSamp
 #pragma unroll
           for (int k = 0; k < 8; ++k) w[k] = x[k] * s;
         },
-        a.share ? row_best_of(a, r) : nullptr, scan, red, red1, &ks, &is, &bad);
+        a.row_best ? a.row_best + r : nullptr, scan, red, red1, &ks, &is, &bad);
   }
   if (threadIdx.x == 0) {
-    GumbelBest& o = a.best[static_cast<int64_t>(r) * P + part];
-    o.kr = ks; o.ir = is; o.ip = bad ? 1 : 0;  // (kp of part 0 is the row's best key)
+    SampleBest o;
+    o.k = ks;
+    o.i = bad ? -1 : is;
+    a.best[static_cast<int64_t>(r) * P + part] = o;
   }
 }
 
@@ -470,13 +473,13 @@ __global__ __launch_bounds__(kThreads) void gumbel_sample_finish_kernel(GumbelSa
   const int r = blockIdx.x * kWaves + (threadIdx.x >> 6);
   if (r >= a.R) return;
   const int lane = threadIdx.x & 63;
-  const GumbelBest* gb = a.best + static_cast<int64_t>(r) * a.P;
+  const SampleBest* gb = a.best + static_cast<int64_t>(r) * a.P;
   float k = -INFINITY;
   int i = kNoIndex, bad = 0;
   for (int cc = lane; cc < a.P; cc += 64) {
-    const GumbelBest e = gb[cc];
-    if (e.kr > k) { k = e.kr; i = e.ir; }
-    bad |= e.ip;
+    const SampleBest e = gb[cc];
+    if (e.k > k) { k = e.k; i = e.i; }
+    bad |= e.i < 0 ? 1 : 0;
   }
   wave_argmax(k, i);
   bad = -wave_min_int(-bad);

@@ -420,8 +420,12 @@ spec_status launch_verify(const sv::VerifyArgs& a, int64_t rows, hipStream_t s, 
 // overlaps at B = 256, K = 3, V = 151936: 512 / 768 / 1024 / 1280 / 1600 /
 // 2560 workgroups 158 / 150 / 146 / 147 / 150 / 154 us; the sampler with 768
 // rows: 2560 / 5120 / 7680 workgroups 111 / 106 / 108 us.
+// From B = 1024 on that is one workgroup a row (against one per chunk with every
+// variate drawn, with overlaps, K = 3 bfloat16: B = 1024, V = 151936 949 -> 746
+// us, B = 4096, V = 32000 812 -> 638, B = 8192, V = 8192 438 -> 383).
 constexpr int kScanWgsVerify = 1024;
 constexpr int kScanWgsSample = 5120;
+constexpr int64_t kScanFineChunks = 384;
 int scan_parts(int rows, int C, int wgs) { return std::max(1, std::min(C, (wgs + rows - 1) / rows)); }
 
 template <class E, int NT>
@@ -450,12 +454,20 @@ spec_status launch_verify_gumbel(const sv::VerifyArgs& a, sv::GumbelBest* gbest,
 
 template <class E>
 spec_status launch_sample_gumbel(sv::GumbelSampleArgs a, hipStream_t s) {
-  a.P = scan_parts(a.R, a.rows.C, kScanWgsSample);
+  // at most a part per chunk, in the smallest calls two, of at least a tile (the
+  // workspace holds 16 bytes per chunk, a part takes 8 and, where the row's
+  // parts share their best key, the row 4).  Flat rows, one part per chunk /
+  // two, us a call: R = 8, V = 32000 15.7 / 13.0, R = 64, V = 65536 (256 chunks)
+  // 16.2 / 14.5, but R = 64, V = 262144 (1024) 27.9 / 29.2, R = 256, V = 65536
+  // 28.1 / 28.8 and with spread rows 24.4 / 28.0.
+  const int tiles = (a.rows.V + sv::kScanTile - 1) / sv::kScanTile;
+  const bool fine = int64_t{a.R} * a.rows.C <= kScanFineChunks;
+  a.P = scan_parts(a.R, fine ? std::min(tiles, 2 * a.rows.C) : a.rows.C, kScanWgsSample);
   // parts beyond the first round of what the device holds start with the best
   // key of the earlier ones (rows with one dominant token 127 -> 87 us; one
   // more small launch)
-  a.share = a.P > 1 && int64_t{a.R} * a.P > 1280 ? 1 : 0;
-  if (a.share)
+  a.row_best = a.P > 1 && int64_t{a.R} * a.P > 1280 ? reinterpret_cast<int*>(a.best + int64_t{a.R} * a.P) : nullptr;
+  if (a.row_best)
     hipLaunchKernelGGL(sv::gumbel_sample_init_kernel, dim3(static_cast<unsigned>((a.R + sv::kThreads - 1) / sv::kThreads)),
                        dim3(sv::kThreads), 0, s, a);
   hipLaunchKernelGGL((sv::gumbel_sample_pass_kernel<E>), dim3(static_cast<unsigned>(int64_t{a.R} * a.P)),
@@ -986,7 +998,7 @@ spec_status spec_sample_gumbel(const void* logits, int64_t stride_r, spec_dtype 
   a.R = R;
   a.seed = seed; a.offset = offset;
   a.token = tokens;
-  a.best = reinterpret_cast<sv::GumbelBest*>(workspace);
+  a.best = reinterpret_cast<sv::SampleBest*>(workspace);
   hipStream_t s = static_cast<hipStream_t>(stream);
   return dtype == SPEC_BF16 ? launch_sample_gumbel<BF16>(a, s) : launch_sample_gumbel<F32>(a, s);
 }
