@@ -48,8 +48,8 @@
  *    left, with the same bits.  No other launch waits on another workgroup.
  *  - Entry points are thread-safe; each call is independent.
  *  - Logits are bfloat16 (raw 16-bit patterns) or float32.  Arithmetic is
- *    float32 per element with float64 accumulation across vectors, threads
- *    and workgroups.
+ *    float32 per element; sums are float32 over at most 128 elements of one
+ *    thread (64 outside the row statistics) and float64 beyond.
  */
 #ifndef SPECVERIFY_H
 #define SPECVERIFY_H

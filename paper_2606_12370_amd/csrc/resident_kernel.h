@@ -520,7 +520,7 @@ __device__ __forceinline__ bool res_position(const TvArgs& a, const ResArgs& r, 
 // 151936, G = 2), 15 write the gradient and issue the next loads, 8 wait for
 // those and sum the statistics, 7 are the second sums' arithmetic and 6 the
 // two exchanges (time stamps per phase).  N = 4096, K = 3, V = 151936: 4.82
-// -> 3.49 ms a call in bfloat16; N = 1024 in float32 1.92 -> 1.30 ms.
+// -> 3.50 ms a call in bfloat16; N = 1024 in float32 1.92 -> 1.25 ms.
 template <class E, int NV>
 __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, ResArgs r) {
   __shared__ ResLds sh;

@@ -247,6 +247,21 @@ def test_verify_scan_parts_without_residual_mass(V):
     print(compare_verify_gumbel(out, ref, W.F32))
 
 
+@pytest.mark.parametrize("R,V", [(96, 4 * 16384), (97, 4 * 16384), (384, 4100), (3, 16384 + 1)])
+def test_sampler_parts_rule(R, V):
+    """Either side of the calls whose rows are scanned in half chunks, and rows
+    with fewer tiles than such parts: the tokens of the oracle."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(R + V)
+    z = torch.randn((R, V), device="cuda", generator=g) * torch.linspace(0.5, 8.0, R, device="cuda")[:, None]
+    out = binding.sample_gumbel(z, 0.9, seed=5, offset=7)["tokens"]
+    torch.cuda.synchronize()
+    rows = np.unique(np.linspace(0, R - 1, 12).astype(int))
+    ref = sample_gumbel_ref(z[torch.as_tensor(rows, device="cuda")].cpu().numpy().astype(np.float64),
+                            np.full(len(rows), float(np.float32(0.9))), 5, 7, rows=rows)
+    compare_sample_gumbel(out, ref, rows=rows)
+
+
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
 @pytest.mark.parametrize("V", [5, 2049, 40000])
 def test_sampler_overflowing_scale(V, dtype):

@@ -165,9 +165,10 @@ def test_target_masked_tokens(mode, dtype):
     (2, 8, 262144, W.F32),        # more slices than a position may take: the two-read passes
 ])
 def test_single_read_edges(N, K, V, dtype, mode):
-    """The gradient call over aligned rows at the edges of its tiles, slices
-    and position groups, against the oracle (a few positions of the long
-    calls), and twice the same bits."""
+    """The gradient call at the edges of the single-read pass's tiles, slices
+    and position groups, rows at any alignment among them, and just beyond the
+    slices it takes, against the oracle (a few positions of the long calls),
+    and twice the same bits."""
     g = np.random.default_rng(V + K)
     d = W.tv_inputs_numpy(N, K, V, dtype, 900 + K, noise=g.uniform(0.05, 2.0, N))
     tgt, drf = device_inputs(d)
