@@ -313,11 +313,16 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
   o.kp = -1.f;
   o.ip = kNoIndex;
   if (residual) {
-    double al = 0.0;  // the eight elements of a block are summed in float32, blocks in float64
+    // float32 over eight blocks (64 elements) of a thread, float64 beyond, like the
+    // other steps' overlaps (float64 from each block on: the sum keeps the
+    // exponentials' common error, +6e-8, of which the rounding of the float32
+    // sums hides a third)
+    double al = 0.0;
+    float sum = 0.f;
+    int blocks = 0;
     gumbel_scan<E, KeyRatio, true>(
         rt, rd, e0, e1, d.V, static_cast<uint64_t>(b), a.offset, kTagGumbelVerify, a.seed,
         [&](const float (&x)[8], const float (&y)[8], float (&r)[8]) {
-          float sum = 0.f;
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const float p = prob(x[k], s, nt.M, nt.invD);
@@ -325,11 +330,14 @@ __global__ __launch_bounds__(kThreads) void gumbel_pass_kernel(VerifyArgs a, Gum
             r[k] = p - mn;
             sum += mn;
           }
-          al += static_cast<double>(sum);
+          if ((++blocks & 7) == 0) {
+            al += static_cast<double>(sum);
+            sum = 0.f;
+          }
         },
         nullptr, scan, red, red1, &o.kr, &o.ir, &bad);
     if (a.overlap) {  // the step's overlap over this part (pair_pass_kernel leaves the step out)
-      double v[4] = {al, 0.0, 0.0, 0.0};
+      double v[4] = {al + static_cast<double>(sum), 0.0, 0.0, 0.0};
       wg_sum<4>(v, red);
       if (threadIdx.x == 0) a.pairs[(static_cast<int64_t>(b) * K + n) * d.C + part].alpha = v[0];
     }
