@@ -134,7 +134,6 @@ struct ResLds {
   float c[8];   // rt, rd, tau, -, A1, A0
   double cc[2]; // cT, cD
   uint32_t ticket;
-  uint32_t arrival;  // the group's state before this workgroup arrived
   int fail;
 };
 
@@ -361,8 +360,7 @@ __device__ __forceinline__ bool res_position(const TvArgs& a, const ResArgs& r, 
                  lane == 0 ? res_word(m2[0], m2[1]) : (lane == 1 ? res_word(D2[0]) : res_word(D2[1])));
       if (ALONE && stages == 1) return true;
     }
-    ok = !first || sh.arrival + 1u < kResGaveUp;  // (given up before this workgroup started)
-    if (G > 1 && ok) {
+    if (G > 1) {
       uint64_t v[3];
       ok = res_wait<ALONE>(r, grp, PG, first, rec + lane * kResWords, lane < G, v);
       const bool on = lane < G;
@@ -534,7 +532,10 @@ __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, R
   const int tk = __builtin_amdgcn_readfirstlane(static_cast<int>(sh.ticket));
   const int grp = tk / PG;
   const ResSlice c = res_slice_of<E, NV>(r, tk - grp * PG, d.V);
-  const uint32_t arrival = threadIdx.x == 0 ? atomicAdd(r.state + grp, 1u) : 0u;
+  // (the old value is not asked for: to read it would wait for all of the loads
+  // below, whose number varies; a group that has given up never passes its
+  // first wait)
+  if (threadIdx.x == 0) atomicAdd(r.state + grp, 1u);
   typename E::vec xt[NV], xd[NV];
 #pragma unroll
   for (int j = 0; j < NV; ++j) xt[j] = xd[j] = res_neg_inf(static_cast<const E*>(nullptr));
@@ -547,7 +548,6 @@ __global__ __launch_bounds__(kResThreads, 2) void tv_resident_kernel(TvArgs a, R
         xd[j] = res_tile_load<E, NV>(c, rd, j, d.V);
       }
   }
-  if (threadIdx.x == 0) sh.arrival = arrival;  // (behind the loads: the atomic is on its way)
   for (int n = grp; n < a.N; n += r.groups)
     if (!res_position<E, NV, false>(a, r, c, n, n + r.groups, grp, 3, xt, xd, sh)) return;
 }
